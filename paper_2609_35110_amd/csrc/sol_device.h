@@ -129,6 +129,30 @@ __device__ __forceinline__ float f32_round_odd(double d) {
   return __uint_as_float(u);
 }
 
+// cos and sin of the 4 pairs of one 16-byte chunk, hi + lo (exact in fp64:
+// |lo| <= half an fp32 ulp of hi).  They depend on the token and the chunk
+// alone, so a kernel that walks the heads of a token loads them once.
+struct RopeCS {
+  double c[4], s[4];
+};
+__device__ __forceinline__ RopeCS load_rope_cs(const float2* __restrict__ hi, const float2* __restrict__ lo,
+                                               int pair0) {
+  const float4 h01 = *reinterpret_cast<const float4*>(hi + pair0);
+  const float4 h23 = *reinterpret_cast<const float4*>(hi + pair0 + 2);
+  const float4 l01 = *reinterpret_cast<const float4*>(lo + pair0);
+  const float4 l23 = *reinterpret_cast<const float4*>(lo + pair0 + 2);
+  RopeCS r;
+  r.c[0] = (double)h01.x + (double)l01.x;
+  r.c[1] = (double)h01.z + (double)l01.z;
+  r.c[2] = (double)h23.x + (double)l23.x;
+  r.c[3] = (double)h23.z + (double)l23.z;
+  r.s[0] = (double)h01.y + (double)l01.y;
+  r.s[1] = (double)h01.w + (double)l01.w;
+  r.s[2] = (double)h23.y + (double)l23.y;
+  r.s[3] = (double)h23.w + (double)l23.w;
+  return r;
+}
+
 // Rotate the 4 interleaved pairs of one 16-byte chunk, held as fp32:
 //   (a, b) -> (a cos - b sin, a sin + b cos)
 // in fp64 with cos and sin taken as hi + lo (48 bits), then one rounding to
@@ -136,26 +160,41 @@ __device__ __forceinline__ float f32_round_odd(double d) {
 // lies within about 2^-47 |(a, b)| of a rounding midpoint.  Every rotation of
 // a query or key row in this library goes through this function, except the
 // fused kernel's key tiles (rope_rotate_fast below).
-__device__ __forceinline__ uint4 rope_rotate_exact(const float (&f)[8], const float2* __restrict__ hi,
-                                                   const float2* __restrict__ lo, int pair0) {
-  const float4 h01 = *reinterpret_cast<const float4*>(hi + pair0);
-  const float4 h23 = *reinterpret_cast<const float4*>(hi + pair0 + 2);
-  const float4 l01 = *reinterpret_cast<const float4*>(lo + pair0);
-  const float4 l23 = *reinterpret_cast<const float4*>(lo + pair0 + 2);
-  // hi + lo is exact in fp64 (|lo| <= half an fp32 ulp of hi)
-  const double c[4] = {(double)h01.x + (double)l01.x, (double)h01.z + (double)l01.z,
-                       (double)h23.x + (double)l23.x, (double)h23.z + (double)l23.z};
-  const double s[4] = {(double)h01.y + (double)l01.y, (double)h01.w + (double)l01.w,
-                       (double)h23.y + (double)l23.y, (double)h23.w + (double)l23.w};
-  uint32_t w[4];
+//
+// The kernels that call this are bound by the number of VALU instructions
+// (fp64 fma, mul and the conversions issue at the fp32 rate: 4.8 clocks a
+// wave, measured), so the rounding to odd, about ten instructions a value, is
+// kept off the common path: rounding the double to fp32 and that to bf16 (both
+// nearest even) differs from rounding it once only where the fp32 value is a
+// bf16 midpoint, low half 0x8000 -- the smallest int16, so one packed minimum
+// a value finds it.  One chunk in 8192 takes the second path.  13 instructions
+// a pair against 29 (both without the table's conversions).
+__device__ __forceinline__ uint4 rope_rotate(const float (&f)[8], const RopeCS& cs) {
+  typedef short i16x2 __attribute__((ext_vector_type(2)));
+  double r[8];
+  float y[8];
+  i16x2 low = {0x7FFF, 0x7FFF};
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const double a = f[2 * u], b = f[2 * u + 1];
-    const double ar = __builtin_fma(a, c[u], -(b * s[u]));
-    const double br = __builtin_fma(a, s[u], b * c[u]);
-    w[u] = pack_bf16x2(f32_round_odd(ar), f32_round_odd(br));
+    r[2 * u] = __builtin_fma(a, cs.c[u], -(b * cs.s[u]));
+    r[2 * u + 1] = __builtin_fma(a, cs.s[u], b * cs.c[u]);
   }
-  return make_uint4(w[0], w[1], w[2], w[3]);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    y[e] = (float)r[e];
+    low = __builtin_elementwise_min(low, __builtin_bit_cast(i16x2, y[e]));
+  }
+  if (__builtin_expect(low[0] == -0x8000, 0)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = f32_round_odd(r[e]);
+  }
+  return pack_bf16x8(y);
+}
+
+__device__ __forceinline__ uint4 rope_rotate_exact(const float (&f)[8], const float2* __restrict__ hi,
+                                                   const float2* __restrict__ lo, int pair0) {
+  return rope_rotate(f, load_rope_cs(hi, lo, pair0));
 }
 
 __device__ __forceinline__ uint4 rope_chunk(uint4 x, const float2* __restrict__ hi,
@@ -227,36 +266,62 @@ __device__ __forceinline__ float chunk_sumsq(uint4 x) {
   for (int e = 1; e < 8; ++e) s = __builtin_fmaf(f[e], f[e], s);
   return s;
 }
-// The tree over 16 consecutive lanes that hold chunks 0..15 of one row.
+// Lane exchanges inside 16 aligned lanes as DPP operands of the VALU (a
+// ds_bpermute, which __shfl_xor is, costs an LDS round trip).
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // lane ^ 7, lane ^ 15
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
+}
+// The tree over 16 consecutive lanes that hold chunks 0..15 of one row.  The
+// mirrors stand for xor 4 and xor 8: by then all lanes of a quad (an 8) hold
+// the same sum.
 __device__ __forceinline__ float row_sumsq_lanes16(float p) {
-  p += __shfl_xor(p, 1);
-  p += __shfl_xor(p, 2);
-  p += __shfl_xor(p, 4);
-  p += __shfl_xor(p, 8);
+  p += dpp<kDppXor1>(p);
+  p += dpp<kDppXor2>(p);
+  p += dpp<kDppHalfMirror>(p);
+  p += dpp<kDppMirror>(p);
   return p;
 }
 __device__ __forceinline__ float rms_inv(float sumsq, float eps) {
   return 1.0f / __builtin_sqrtf(sumsq * (1.0f / D) + eps);
 }
-// Chunk cc (dims 8cc..8cc+7) of a row, normalised: (x inv) gamma, fp32.
-__device__ __forceinline__ void norm_chunk(uint4 x, float inv, const float* __restrict__ gamma,
-                                           int cc, float (&f)[8]) {
-  unpack_bf16x8(x, f);
+// The 8 norm weights of chunk cc (dims 8cc..8cc+7).
+__device__ __forceinline__ void load_gamma(const float* __restrict__ gamma, int cc, float (&gm)[8]) {
   const float4 g0 = *reinterpret_cast<const float4*>(gamma + 8 * cc);
   const float4 g1 = *reinterpret_cast<const float4*>(gamma + 8 * cc + 4);
-  const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+  gm[0] = g0.x; gm[1] = g0.y; gm[2] = g0.z; gm[3] = g0.w;
+  gm[4] = g1.x; gm[5] = g1.y; gm[6] = g1.z; gm[7] = g1.w;
+}
+// A chunk of a row, normalised: (x inv) gamma, fp32.
+__device__ __forceinline__ void norm_chunk(uint4 x, float inv, const float (&gm)[8], float (&f)[8]) {
+  unpack_bf16x8(x, f);
 #pragma unroll
   for (int e = 0; e < 8; ++e) f[e] = (f[e] * inv) * gm[e];
 }
-// Chunk cc of a query or key row as it enters the products: normalised when
-// gamma is given (inv from the row's sum of squares), rotated when rot (table
-// pairs from pair0 in planes hi and lo), rounded to bf16.
+// A chunk of a query or key row as it enters the products: normalised when
+// kNorm (inv from the row's sum of squares), rotated when kRope and rot (a
+// lane's own; the rotation runs either way), rounded to bf16.
+template <bool kRope, bool kNorm>
+__device__ __forceinline__ uint4 qk_chunk(uint4 x, const float (&gm)[8], float inv, bool rot, const RopeCS& cs) {
+  float f[8];
+  if (kNorm) norm_chunk(x, inv, gm, f);
+  else unpack_bf16x8(x, f);
+  const uint4 plain = kNorm ? pack_bf16x8(f) : x;
+  if (!kRope) return plain;
+  const uint4 y = rope_rotate(f, cs);
+  return make_uint4(rot ? y.x : plain.x, rot ? y.y : plain.y, rot ? y.z : plain.z, rot ? y.w : plain.w);
+}
+// The same for chunk cc with its weights and table pairs (from pair0 in planes
+// hi and lo) read here.
 __device__ __forceinline__ uint4 qk_chunk(uint4 x, const float* __restrict__ gamma, float inv, int cc,
                                           bool rot, const float2* __restrict__ hi,
                                           const float2* __restrict__ lo, int pair0) {
   if (gamma == nullptr) return rot ? rope_chunk(x, hi, lo, pair0) : x;
-  float f[8];
-  norm_chunk(x, inv, gamma, cc, f);
+  float f[8], gm[8];
+  load_gamma(gamma, cc, gm);
+  norm_chunk(x, inv, gm, f);
   if (!rot) return pack_bf16x8(f);
   return rope_rotate_exact(f, hi, lo, pair0);
 }

@@ -69,11 +69,17 @@ __device__ __forceinline__ void note_range(bool bad, unsigned flag) {
 
 // --------------------------------------------------------- standalone rotary
 
-// One thread per 16-byte chunk of one (b, h) slab; grid.y walks the slabs.
-// gamma != NULL: each row is RMS-normalised first (the 16 chunks of a row sit
-// in 16 consecutive lanes; rows are never split across waves).
+// One thread per 16-byte chunk of a token's row, for `per_wg` slabs in a row
+// (grid.y walks the groups of slabs): the token's position and its cosines and
+// sines, 30 or so instructions beside the 90 of a normalised rotation, are the
+// same in every slab.  The next slab's load is issued ahead of this one's
+// arithmetic.  kNorm: each row is RMS-normalised first (the 16 chunks of a row
+// sit in 16 consecutive lanes; rows are never split across waves).  Streams:
+// 40 slabs of 28,800 tokens, normalised, take 107 us = 5.5 TB/s, the rate of a
+// plain copy of that size (155 us with the position and the table per slab).
+template <bool kRope, bool kNorm>
 __global__ __launch_bounds__(256) void rope3d_kernel(const uint4* __restrict__ x,
-                                                     uint4* __restrict__ y, int64_t bh_count,
+                                                     uint4* __restrict__ y, int64_t bh_count, int per_wg,
                                                      SeqGrid g, const float2* __restrict__ tab,
                                                      const float* __restrict__ gamma, float eps) {
   const int64_t per_slab = (int64_t)g.n * kChunks;
@@ -81,14 +87,32 @@ __global__ __launch_bounds__(256) void rope3d_kernel(const uint4* __restrict__ x
   if (i >= per_slab) return;  // whole rows: the lanes of a row leave together
   const int n = (int)(i / kChunks);
   const int cc = (int)(i % kChunks);
-  const Pos p = token_pos(n, g);
-  const bool rot = p.rot && tab != nullptr;
-  const int pair0 = rot ? tab_pair(cc, p, g) : 0;
-  for (int64_t bh = blockIdx.y; bh < bh_count; bh += gridDim.y) {
-    const int64_t idx = bh * per_slab + i;
-    const uint4 v = x[idx];
-    const float inv = gamma ? rms_inv(row_sumsq_lanes16(chunk_sumsq(v)), eps) : 1.0f;
-    y[idx] = qk_chunk(v, gamma, inv, cc, rot, tab, tab_lo_plane(tab, g), pair0);
+  Pos p{0, 0, 0, false};
+  RopeCS cs{};
+  float gm[8] = {};
+  if (kRope) {
+    p = token_pos(n, g);
+    cs = load_rope_cs(tab, tab_lo_plane(tab, g), tab_pair(cc, p, g));
+  }
+  if (kNorm) load_gamma(gamma, cc, gm);
+  for (int64_t bh0 = (int64_t)blockIdx.y * per_wg; bh0 < bh_count; bh0 += (int64_t)gridDim.y * per_wg) {
+    const int slabs = (int)min((int64_t)per_wg, bh_count - bh0);
+    const uint4* __restrict__ xs = x + bh0 * per_slab + i;
+    uint4* __restrict__ ys = y + bh0 * per_slab + i;
+    auto step = [&](int u, const uint4& cur) __attribute__((always_inline)) {
+      const float inv = kNorm ? rms_inv(row_sumsq_lanes16(chunk_sumsq(cur)), eps) : 1.0f;
+      ys[u * per_slab] = qk_chunk<kRope, kNorm>(cur, gm, inv, p.rot, cs);
+    };
+    uint4 a = xs[0];
+    // two a trip: no load in flight moves between registers (and none hangs on
+    // a branch, which would make the compiler wait for it there; past the last
+    // slab it reads that one again)
+    for (int u = 0; u < slabs; u += 2) {
+      const uint4 b = xs[min(u + 1, slabs - 1) * per_slab];
+      step(u, a);
+      a = xs[min(u + 2, slabs - 1) * per_slab];
+      if (u + 1 < slabs) step(u + 1, b);
+    }
   }
 }
 
@@ -107,22 +131,60 @@ __global__ __launch_bounds__(256) void rope3d_kernel(const uint4* __restrict__ x
 // of a prepared sequence of n_kv keys (several calls fill one sequence from
 // several sources, e.g. cached reference keys and the current step's).  Keys
 // past n_kv are zero.  A tile that also holds keys of another source is
-// written element by element, only where this call owns the key.  One
-// workgroup per tile (from tile0 on); grid.y walks the slabs.
+// written element by element, only where this call owns the key.
+//
+// One workgroup per tile (from tile0 on) and group of `per_wg` slabs (grid.y
+// walks the groups), one 16-byte chunk of K and one of V per thread and slab.
+// The pass streams: its floor is k and v read and the tiles written.  What it
+// must not add to that is instructions and scattered stores, so the token's
+// position, cosines and sines are found once for the group's slabs, the next
+// slab's chunks are loaded ahead of this one's arithmetic, and both tiles
+// leave as whole 1 KB wave stores: K through LDS ([chunk][key], which is the
+// tile's own order, rows padded by a chunk so that neither side conflicts), V
+// through LDS transpose reads.  One barrier per slab (two LDS buffers).
+constexpr int kPrepThreads = kPrepTile * kChunks;  // 512
+constexpr int kKCol = kPrepTile + 1;               // K staging: chunks per column
+constexpr int kVRow = D + 32;                      // V staging: elements per row (320 B)
 
-template <bool kRope, bool kRec>
-__global__ __launch_bounds__(256) void prep_kv_kernel(const uint4* __restrict__ k,
+// Largest fp16 magnitude seen, two packed halves: a value that is inf or NaN
+// has a magnitude of at least 0x7C00.
+struct RangeMax {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 m = {0, 0};
+  __device__ __forceinline__ void add(uint4 x) {
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[u] & 0x7FFF7FFFu));
+  }
+  __device__ __forceinline__ bool nonfinite() const {
+    const uint32_t w = opaque_bits(__builtin_bit_cast(uint32_t, m));
+    return (w & 0xFFFFu) >= 0x7C00u || (w >> 16) >= 0x7C00u;
+  }
+};
+
+// Eight fp16 of one column of a staged V tile, keys p .. p + 3 and p + 8 ..
+// p + 11 of it (a transpose read gives four rows of a column).
+__device__ __forceinline__ uint4 column_frag(const uint16_t* p) {
+  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
+  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 8 * kVRow));
+  return __builtin_bit_cast(uint4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <bool kRope, bool kNorm, bool kRec>
+__global__ __launch_bounds__(kPrepThreads) void prep_kv_kernel(const uint4* __restrict__ k,
                                                       const uint4* __restrict__ v,
                                                       uint4* __restrict__ kp, uint4* __restrict__ vp,
-                                                      int64_t bh_count, SeqGrid g,
+                                                      int64_t bh_count, int per_wg, SeqGrid g,
                                                       const float2* __restrict__ tab, int key0,
                                                       int n_kv, int tile0,
                                                       const float* __restrict__ gamma, float eps,
                                                       const uint8_t* __restrict__ rec, int heads) {
-  __shared__ __attribute__((aligned(16))) uint16_t vt[kPrepTile * (D + 8)];
-  lds_poison(vt, sizeof(vt));
+  __shared__ __attribute__((aligned(16))) uint4 kt_lds[2][kChunks * kKCol];
+  __shared__ __attribute__((aligned(16))) uint16_t vt_lds[2][kPrepTile * kVRow];
+  lds_poison(kt_lds, sizeof(kt_lds));
+  lds_poison(vt_lds, sizeof(vt_lds));
   lds_poison_done();
-  const float2* __restrict__ tab_lo = tab_lo_plane(tab, g);
   const int n_src = g.n;
   const int n_tiles = (n_kv + kPrepTile - 1) / kPrepTile;  // tiles per prepared slab
   const int tile = tile0 + blockIdx.x;
@@ -132,79 +194,109 @@ __global__ __launch_bounds__(256) void prep_kv_kernel(const uint4* __restrict__ 
   // (key0 <= dst < key0 + n_src) or padding past the sequence (dst >= n_kv).
   auto owned = [&](int dst) { return (dst >= key0 && dst - key0 < n_src) || dst >= n_kv; };
   const bool whole = first >= key0 && min(first + kPrepTile, n_kv) <= key0 + n_src;
-  // This thread's two 16-byte chunks of the tile: row r, chunk cc (dims 8cc..8cc+7).
-  int r[2], cc[2], pair0[2], src[2];
-  bool valid[2], rot[2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = t + 256 * u;
-    r[u] = c >> 4;
-    cc[u] = c & 15;
-    src[u] = first + r[u] - key0;
-    valid[u] = src[u] >= 0 && src[u] < n_src;
-    Pos p{0, 0, 0, false};
-    if (kRope && valid[u]) p = token_pos(src[u], g);
-    rot[u] = kRope && p.rot;
-    pair0[u] = rot[u] ? tab_pair(cc[u], p, g) : 0;
+  // This thread's chunk of the source rows: row r, chunk cc (dims 8cc..8cc+7).
+  const int r = t >> 4, cc = t & 15;
+  const int own = first + r - key0;
+  const bool valid = own >= 0 && own < n_src;
+  const int src = min(max(own, 0), n_src - 1);  // a row to read where this is none of them
+  Pos p{0, 0, 0, false};
+  RopeCS cs{};
+  float gm[8] = {};
+  if (kRope) {
+    p = token_pos(src, g);
+    cs = load_rope_cs(tab, tab_lo_plane(tab, g), tab_pair(cc, p, g));
   }
+  if (kNorm) load_gamma(gamma, cc, gm);
+  // Its 16 bytes of the tiles: K chunk t >> 5 of key t & 31 (slot t), and slot
+  // t of V: wave j = 4 kst + db, lane l + 32 h.
+  const int k_read = (t >> 5) * kKCol + (t & 31);
+  const int lane = t & 63, j = t >> 6;
+  const int kst = j >> 2, db = j & 3, h = lane >> 5;
+  // the transpose read's addresses: in each 16-lane group lane 4s + c supplies
+  // row s (of 4) and 4 columns starting at 4c
+  const int g16 = lane >> 4, i16 = lane & 15;
+  const int v_read = (16 * kst + 4 * (g16 >> 1) + (i16 >> 2)) * kVRow + 32 * db + 16 * (g16 & 1) + 4 * (i16 & 3);
+
   const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-  bool bad_k = false, bad_v = false;  // an fp16 operand out of range (or not finite)
-  for (int64_t bh = blockIdx.y; bh < bh_count; bh += gridDim.y) {
-    const size_t row0 = (size_t)bh * n_src;
-    uint4* kt = kp + ((size_t)bh * n_tiles + tile) * (kPrepTileElems / 8);
-    uint4* vtile = vp + ((size_t)bh * n_tiles + tile) * (kPrepTileElems / 8);
-    // kRec: the keys and values come decoded from the block-INT8 records of
-    // the (b, h) slab, token-major with `heads` records per token
-    const int64_t rb = kRec ? bh / heads : 0;
-    const size_t rslab = kRec ? (size_t)rb * n_src * heads + (size_t)(bh - rb * heads) : 0;
-    auto rec_of = [&](int u) { return rec + (rslab + (size_t)src[u] * heads) * kRecBytes; };
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
+  RangeMax range_k, range_v;  // an fp16 operand out of range (or not finite)
+  for (int64_t bh0 = (int64_t)blockIdx.y * per_wg; bh0 < bh_count; bh0 += (int64_t)gridDim.y * per_wg) {
+    const int slabs = (int)min((int64_t)per_wg, bh_count - bh0);
+    // One slab's K and V of this thread: bf16 chunks, or (kRec) the codes and
+    // scale bytes of the (b, h) slab's records, token-major with `heads`
+    // records per token
+    struct In {
+      uint4 k, v;
+      uint32_t ks, vs;
+    };
+    auto load = [&](int u) __attribute__((always_inline)) {
+      In in{zero, zero, 0u, 0u};
+      const int64_t bh = bh0 + u;
+      if (kRec) {
+        const int64_t b = bh / heads;
+        const uint8_t* rp = rec + (((size_t)b * n_src + src) * heads + (bh - b * heads)) * kRecBytes;
+        const uint2 kc = *reinterpret_cast<const uint2*>(rp + 128 + 8 * cc);
+        const uint2 vc = *reinterpret_cast<const uint2*>(rp + 256 + 8 * cc);
+        in.k = make_uint4(kc.x, kc.y, 0u, 0u);
+        in.v = make_uint4(vc.x, vc.y, 0u, 0u);
+        in.ks = rp[kRecScales + 4 + (cc >> 2)];
+        in.vs = rp[kRecScales + 8 + (cc >> 2)];
+      } else {
+        const size_t at = ((size_t)bh * n_src + src) * kChunks + cc;
+        in.k = k[at];
+        in.v = v[at];
+      }
+      return in;
+    };
+    auto step = [&](int u, uint4* __restrict__ kt, uint16_t* __restrict__ vt, const In& in)
+        __attribute__((always_inline)) {
+      uint4 kx, vx;
       if (kRec) {
         // records carry k as attention consumes it (normalised and rotated)
-        const uint4 xr = valid[u] ? rec_chunk(rec_of(u), 1, cc[u]) : zero;
-        const uint4 xh = bf16x8_to_f16x8(xr);
-        bad_k |= f16x8_nonfinite(xh);
-        if (owned(first + r[u])) kt[(cc[u] >> 1) * 64 + r[u] + 32 * (cc[u] & 1)] = xh;
+        kx = decode_rec_chunk(make_uint2(in.k.x, in.k.y), ue5m3_value(in.ks));
+        vx = decode_rec_chunk(make_uint2(in.v.x, in.v.y), ue5m3_value(in.vs));
       } else {
-        const uint4 x = valid[u] ? k[(row0 + src[u]) * kChunks + cc[u]] : zero;
-        // every lane takes part in the row sums (rows sit in 16 aligned lanes)
-        const float inv = gamma ? rms_inv(row_sumsq_lanes16(chunk_sumsq(x)), eps) : 1.0f;
-        const uint4 xr = valid[u] ? qk_chunk(x, gamma, inv, cc[u], rot[u], tab, tab_lo, pair0[u]) : zero;
-        const uint4 xh = bf16x8_to_f16x8(xr);
-        bad_k |= f16x8_nonfinite(xh);
-        if (owned(first + r[u])) kt[(cc[u] >> 1) * 64 + r[u] + 32 * (cc[u] & 1)] = xh;
+        const float inv = kNorm ? rms_inv(row_sumsq_lanes16(chunk_sumsq(in.k)), eps) : 1.0f;
+        kx = qk_chunk<kRope, kNorm>(in.k, gm, inv, p.rot, cs);
+        vx = in.v;
       }
-      const uint4 y = !valid[u] ? zero
-                      : kRec    ? rec_chunk(rec_of(u), 2, cc[u])
-                                : v[(row0 + src[u]) * kChunks + cc[u]];
-      const uint4 yh = bf16x8_to_f16x8(y);
-      bad_v |= f16x8_nonfinite(yh);
-      *reinterpret_cast<uint4*>(&vt[r[u] * (D + 8) + cc[u] * 8]) = yh;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = t + 256 * u;
-      const int j = c >> 6, ln = c & 63;
-      const int kst = j >> 2, db = j & 3, l = ln & 31, h = ln >> 5;
-      const uint16_t* col = vt + (16 * kst + 4 * h) * (D + 8) + 32 * db + l;
-      auto key = [&](int i) { return 16 * kst + 4 * h + 8 * (i >> 2) + (i & 3); };
-      auto el = [&](int i) { return (uint32_t)col[(8 * (i >> 2) + (i & 3)) * (D + 8)]; };
+      const uint4 kh = bf16x8_to_f16x8(valid ? kx : zero), vh = bf16x8_to_f16x8(valid ? vx : zero);
+      range_k.add(kh);
+      range_v.add(vh);
+      kt[cc * kKCol + r] = kh;
+      *reinterpret_cast<uint4*>(&vt[r * kVRow + cc * 8]) = vh;
+      __syncthreads();
+      const size_t out = (((size_t)(bh0 + u)) * n_tiles + tile) * (kPrepTileElems / 8) + t;
+      const uint4 ko = kt[k_read];
+      const uint4 vo = column_frag(vt + v_read);
       if (whole) {
-        vtile[c] = make_uint4(el(0) | el(1) << 16, el(2) | el(3) << 16, el(4) | el(5) << 16,
-                              el(6) | el(7) << 16);
+        kp[out] = ko;
+        vp[out] = vo;
       } else {
-        uint16_t* dst = reinterpret_cast<uint16_t*>(vtile + c);
+        if (owned(first + (t & 31))) kp[out] = ko;
+        uint16_t* dst = reinterpret_cast<uint16_t*>(vp + out);
+        const uint32_t w[4] = {vo.x, vo.y, vo.z, vo.w};
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          if (owned(first + key(i))) dst[i] = (uint16_t)el(i);
+          if (owned(first + 16 * kst + 4 * h + 8 * (i >> 2) + (i & 3))) dst[i] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
       }
+    };
+    // Two steps a trip, so that neither the loads in flight nor the buffers
+    // move between registers (and no load hangs on a branch, which would make
+    // the compiler wait for it there; past the last slab it reads that one
+    // again).  A buffer is written again two steps later,
+    // after the next step's barrier, which every wave reaches with its reads
+    // of it done.
+    In a = load(0);
+    for (int u = 0; u < slabs; u += 2) {
+      const In b = load(min(u + 1, slabs - 1));
+      step(u, kt_lds[0], vt_lds[0], a);
+      a = load(min(u + 2, slabs - 1));
+      if (u + 1 < slabs) step(u + 1, kt_lds[1], vt_lds[1], b);
     }
-    __syncthreads();
+    __syncthreads();  // the next group starts with buffer 0 again
   }
-  note_range(bad_k, SOL_RANGE_K);
-  note_range(bad_v, SOL_RANGE_V);
+  note_range(range_k.nonfinite(), SOL_RANGE_K);
+  note_range(range_v.nonfinite(), SOL_RANGE_V);
 }
 
 // ------------------------------------------------------------ fused attention
@@ -1442,15 +1534,30 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 
 }  // namespace
 
+// Workgroups a streaming kernel is given before its workgroups take more slabs
+// each: eight a CU.
+constexpr int64_t kStreamWgs = 2048;
+
+// Slabs per workgroup of the streaming kernels that find a token's rotation
+// once for several slabs: as many as leave `want` workgroups, at most 8 (by
+// then the shared work is an eighth).
+static int slabs_per_workgroup(int64_t tiles, int64_t bh_count, int64_t want) {
+  const int64_t n = tiles * bh_count / want;
+  return (int)(n < 1 ? 1 : n > 8 ? 8 : n);
+}
+
 hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int64_t rows, const SeqGrid& g,
                          const float2* tab, const float* gamma, float eps, hipStream_t stream) {
   const int64_t per_slab = (int64_t)g.n * kChunks;
   const int64_t bh_count = rows / g.n;
   const unsigned gx = (unsigned)((per_slab + 255) / 256);
-  const unsigned gy = (unsigned)(bh_count < 65535 ? bh_count : 65535);
-  hipLaunchKernelGGL(rope3d_kernel, dim3(gx, gy), dim3(256), 0, stream,
-                     reinterpret_cast<const uint4*>(x), reinterpret_cast<uint4*>(y), bh_count, g,
-                     tab, gamma, eps);
+  const int per_wg = slabs_per_workgroup(gx, bh_count, kStreamWgs);
+  const int64_t groups = (bh_count + per_wg - 1) / per_wg;
+  const unsigned gy = (unsigned)(groups < 65535 ? groups : 65535);
+  auto* kernel = tab ? (gamma ? rope3d_kernel<true, true> : rope3d_kernel<true, false>)
+                     : (gamma ? rope3d_kernel<false, true> : rope3d_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(gx, gy), dim3(256), 0, stream, reinterpret_cast<const uint4*>(x),
+                     reinterpret_cast<uint4*>(y), bh_count, per_wg, g, tab, gamma, eps);
   return hipGetLastError();
 }
 
@@ -1473,23 +1580,28 @@ hipError_t launch_attn_fwd(const uint16_t* q, const uint16_t* k, const uint16_t*
   return hipGetLastError();
 }
 
+// The grid of the prepare pass over the tiles that hold keys key0 ..
+// key0 + n - 1, and the slabs per workgroup.
+static dim3 prep_grid(int key0, int n, int BH, int& tile0, int& per_wg) {
+  tile0 = key0 / kPrepTile;
+  const int tiles = (key0 + n - 1) / kPrepTile - tile0 + 1;
+  per_wg = slabs_per_workgroup(tiles, BH, kStreamWgs);
+  const int64_t groups = ((int64_t)BH + per_wg - 1) / per_wg;
+  return dim3((unsigned)tiles, (unsigned)(groups < 65535 ? groups : 65535));
+}
+
 hipError_t launch_prepare_kv(const uint16_t* k, const uint16_t* v, uint16_t* k_prep,
                              uint16_t* v_prep, int BH, const SeqGrid& g, const float2* tab,
                              int key0, int n_kv, const float* gamma, float eps,
                              hipStream_t stream) {
-  const int tile0 = key0 / kPrepTile;
-  const int tile1 = (key0 + g.n - 1) / kPrepTile;  // last tile holding one of these keys
-  const dim3 pgrid((unsigned)(tile1 - tile0 + 1), (unsigned)(BH < 65535 ? BH : 65535));
-  if (tab != nullptr)
-    hipLaunchKernelGGL((prep_kv_kernel<true, false>), pgrid, dim3(256), 0, stream,
-                       reinterpret_cast<const uint4*>(k), reinterpret_cast<const uint4*>(v),
-                       reinterpret_cast<uint4*>(k_prep), reinterpret_cast<uint4*>(v_prep),
-                       (int64_t)BH, g, tab, key0, n_kv, tile0, gamma, eps, nullptr, 1);
-  else
-    hipLaunchKernelGGL((prep_kv_kernel<false, false>), pgrid, dim3(256), 0, stream,
-                       reinterpret_cast<const uint4*>(k), reinterpret_cast<const uint4*>(v),
-                       reinterpret_cast<uint4*>(k_prep), reinterpret_cast<uint4*>(v_prep),
-                       (int64_t)BH, g, tab, key0, n_kv, tile0, gamma, eps, nullptr, 1);
+  int tile0, per_wg;
+  const dim3 grid = prep_grid(key0, g.n, BH, tile0, per_wg);
+  auto* kernel = tab ? (gamma ? prep_kv_kernel<true, true, false> : prep_kv_kernel<true, false, false>)
+                     : (gamma ? prep_kv_kernel<false, true, false> : prep_kv_kernel<false, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kPrepThreads), 0, stream, reinterpret_cast<const uint4*>(k),
+                     reinterpret_cast<const uint4*>(v), reinterpret_cast<uint4*>(k_prep),
+                     reinterpret_cast<uint4*>(v_prep), (int64_t)BH, per_wg, g, tab, key0, n_kv, tile0, gamma,
+                     eps, nullptr, 1);
   return hipGetLastError();
 }
 
@@ -1497,12 +1609,11 @@ hipError_t launch_prepare_kv_records(const uint8_t* rec, uint16_t* k_prep, uint1
                                      int B, int H, int N, int key0, int n_kv, hipStream_t stream) {
   const int BH = B * H;
   const SeqGrid g = make_grid(N, 0, 0, 0);
-  const int tile0 = key0 / kPrepTile;
-  const int tile1 = (key0 + N - 1) / kPrepTile;
-  const dim3 pgrid((unsigned)(tile1 - tile0 + 1), (unsigned)(BH < 65535 ? BH : 65535));
-  hipLaunchKernelGGL((prep_kv_kernel<false, true>), pgrid, dim3(256), 0, stream, nullptr, nullptr,
+  int tile0, per_wg;
+  const dim3 grid = prep_grid(key0, N, BH, tile0, per_wg);
+  hipLaunchKernelGGL((prep_kv_kernel<false, false, true>), grid, dim3(kPrepThreads), 0, stream, nullptr, nullptr,
                      reinterpret_cast<uint4*>(k_prep), reinterpret_cast<uint4*>(v_prep),
-                     (int64_t)BH, g, nullptr, key0, n_kv, tile0, nullptr, 0.0f, rec, H);
+                     (int64_t)BH, per_wg, g, nullptr, key0, n_kv, tile0, nullptr, 0.0f, rec, H);
   return hipGetLastError();
 }
 

@@ -1,0 +1,65 @@
+"""The streaming kernels' grouping of slabs: a workgroup of the standalone
+rotation and of the prepare pass takes one token tile through 1 to 8 (b, h)
+slabs, as many as leave 2048 workgroups.  Whatever the group, every slab's
+bytes are those of a call on that slab alone (a group of one)."""
+import pytest
+import torch
+
+from paper_2609_35110_amd import sol
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+# (slabs, grid, text): tiles of 32 keys x slabs over 2048 gives groups of
+# 1 (one short), 2 with an odd slab over, 3, and the largest, 8
+CASES = [(255, (1, 15, 17), 0), (257, (2, 11, 23), 11), (411, (2, 11, 23), 0), (2051, (1, 16, 16), 3)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    sol.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+def _inputs(slabs, grid, text):
+    n = text + grid[0] * grid[1] * grid[2]
+    gen = torch.Generator(DEV).manual_seed(slabs)
+    k, v = (torch.randn((1, slabs, n, sol.HEAD_DIM), generator=gen, device=DEV).bfloat16() for _ in range(2))
+    gamma = 1 + 0.25 * torch.randn(sol.HEAD_DIM, generator=gen, device=DEV)
+    return n, k, v, gamma
+
+
+@pytest.mark.parametrize("norm", [False, True], ids=["rope", "qknorm+rope"])
+@pytest.mark.parametrize("slabs,grid,text", CASES)
+def test_prepare_groups_of_slabs(slabs, grid, text, norm):
+    """Whole and shared tiles (the source starts at key 21 of a longer
+    sequence): each slab as prepared alone, the keys of others untouched."""
+    n, k, v, gamma = _inputs(slabs, grid, text)
+    gamma = gamma if norm else None
+    tab = sol.rope3d_table(*grid, device=DEV)
+    key0, n_kv = 21, n + 21 + 40
+    kp, vp = (t.fill_(7.0) for t in sol.prepared_kv_buffers(1, slabs, n_kv, DEV))
+    sol.prepare_kv_ex(k, v, *grid, tab, kp, vp, key0, n_kv, gamma)
+    kp, vp = kp.view(slabs, -1), vp.view(slabs, -1)
+    for s in sorted({0, 1, 2, 3, 7, 8, slabs // 2, slabs - 2, slabs - 1}):
+        k1, v1 = (t.fill_(7.0) for t in sol.prepared_kv_buffers(1, 1, n_kv, DEV))
+        sol.prepare_kv_ex(k[:, s:s + 1].contiguous(), v[:, s:s + 1].contiguous(), *grid, tab, k1, v1, key0, n_kv, gamma)
+        assert torch.equal(kp[s].view(torch.int16), k1.view(torch.int16)), s
+        assert torch.equal(vp[s].view(torch.int16), v1.view(torch.int16)), s
+
+
+@pytest.mark.parametrize("norm", [False, True], ids=["rope", "qknorm+rope"])
+@pytest.mark.parametrize("slabs,grid,text", CASES)
+def test_rotation_groups_of_slabs(slabs, grid, text, norm):
+    n, x, _, gamma = _inputs(2 * slabs, grid, text)  # 16 rows a workgroup: twice the tiles
+    tab = sol.rope3d_table(*grid, device=DEV)
+
+    def rotate(t):
+        return sol.qknorm_rope3d(t, *grid, tab, gamma) if norm else sol.rope3d(t, *grid, tab)
+
+    y = rotate(x)
+    for s in sorted({0, 1, 2, 3, 7, 8, slabs, 2 * slabs - 2, 2 * slabs - 1}):
+        one = rotate(x[:, s:s + 1].contiguous())
+        assert torch.equal(y[:, s:s + 1].view(torch.int16), one.view(torch.int16)), s

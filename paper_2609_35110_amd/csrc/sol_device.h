@@ -270,6 +270,8 @@ __device__ __forceinline__ float chunk_sumsq(uint4 x) {
 // ds_bpermute, which __shfl_xor is, costs an LDS round trip).
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // lane ^ 7, lane ^ 15
+constexpr int kDppEven = 0xA0, kDppOdd = 0xF5;             // the pair's even or odd lane
+constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA;  // the quad's lane 0, 1 or 2
 template <int kCtrl>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));

@@ -118,6 +118,18 @@ __host__ __device__ inline int sparse_order_block(int o, int nqb, int stride) {
   return o < rows * stride && b < nqb ? b : -1;
 }
 
+// Workgroups a streaming kernel is given before its workgroups take more slabs
+// each: eight a CU.
+constexpr int64_t kStreamWgs = 2048;
+
+// Slabs per workgroup of the streaming kernels that find a token's rotation
+// once for several slabs: as many as leave `want` workgroups, at most 8 (by
+// then the shared work is an eighth).
+inline int slabs_per_workgroup(int64_t tiles, int64_t bh_count, int64_t want) {
+  const int64_t n = tiles * bh_count / want;
+  return (int)(n < 1 ? 1 : n > 8 ? 8 : n);
+}
+
 // fp16 elements of one (b, h) slab of prepared K (or V).
 inline int64_t prepared_tile_elems(int N) {
   return (int64_t)((N + kPrepTile - 1) / kPrepTile) * kPrepTileElems;

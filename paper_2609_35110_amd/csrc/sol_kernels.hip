@@ -1534,18 +1534,6 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 
 }  // namespace
 
-// Workgroups a streaming kernel is given before its workgroups take more slabs
-// each: eight a CU.
-constexpr int64_t kStreamWgs = 2048;
-
-// Slabs per workgroup of the streaming kernels that find a token's rotation
-// once for several slabs: as many as leave `want` workgroups, at most 8 (by
-// then the shared work is an eighth).
-static int slabs_per_workgroup(int64_t tiles, int64_t bh_count, int64_t want) {
-  const int64_t n = tiles * bh_count / want;
-  return (int)(n < 1 ? 1 : n > 8 ? 8 : n);
-}
-
 hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int64_t rows, const SeqGrid& g,
                          const float2* tab, const float* gamma, float eps, hipStream_t stream) {
   const int64_t per_slab = (int64_t)g.n * kChunks;

@@ -114,6 +114,29 @@ def test_encode_equals_oracle_bytes(shape):
     assert np.array_equal(got, want), "%d of %d bytes differ" % ((got != want).sum(), got.size)
 
 
+def test_quantiser_on_every_scale_and_value():
+    """Every finite bf16 as a group's largest magnitude (the scale), and under
+    every scale code every bf16 from s / 4 to 127 s (the codes: ties, their
+    neighbours, the largest), against the oracle byte for byte."""
+    mags = np.arange(0x7F80, dtype=np.uint16)
+    rng = np.random.default_rng(11)
+    groups = np.zeros((len(mags), 32), np.uint16)
+    groups[np.arange(len(mags)), rng.integers(0, 32, len(mags))] = mags
+    vals = (mags.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    for c in range(1, 0xF8):
+        s = c * 2.0 ** -17 if c < 8 else (1 + (c & 7) / 8) * 2.0 ** ((c >> 3) - 15)
+        at = mags[(vals >= s / 4) & (vals <= 127 * s)]
+        body = np.concatenate([at, np.repeat(at[-1:], -len(at) % 31)]).reshape(-1, 31)
+        groups = np.concatenate([groups, np.concatenate([np.repeat(at[-1:], len(body))[:, None], body], 1)])
+    groups = np.concatenate([groups, np.zeros((-len(groups) % 4, 32), np.uint16)])
+    groups |= rng.integers(0, 2, groups.shape, dtype=np.uint16) << 15
+    x = groups.reshape(1, 1, -1, 128)
+    t = torch.from_numpy(x.view(np.int16)).view(torch.bfloat16).to(DEV)
+    rec = sol.qkv_encode(t, t, t)
+    want = oracle.encode_qkv(x, x, x)
+    assert np.array_equal(rec.cpu().numpy().reshape(want.shape), want)
+
+
 def test_encode_fused_equals_normalise_rotate_then_encode():
     """The encoder's fused normalisation and rotation give the bits of
     sol_qknorm_rope3d: encoding its output without either is byte-identical."""

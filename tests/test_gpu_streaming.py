@@ -1,7 +1,8 @@
 """The streaming kernels' grouping of slabs: a workgroup of the standalone
-rotation and of the prepare pass takes one token tile through 1 to 8 (b, h)
-slabs, as many as leave 2048 workgroups.  Whatever the group, every slab's
-bytes are those of a call on that slab alone (a group of one)."""
+rotation, of the prepare pass and of the record encoder takes one token tile
+through 1 to 8 (b, h) slabs (the encoder: heads), as many as leave 2048
+workgroups.  Whatever the group, every slab's bytes are those of a call on
+that slab alone (a group of one)."""
 import pytest
 import torch
 
@@ -63,3 +64,19 @@ def test_rotation_groups_of_slabs(slabs, grid, text, norm):
     for s in sorted({0, 1, 2, 3, 7, 8, slabs, 2 * slabs - 2, 2 * slabs - 1}):
         one = rotate(x[:, s:s + 1].contiguous())
         assert torch.equal(y[:, s:s + 1].view(torch.int16), one.view(torch.int16)), s
+
+
+@pytest.mark.parametrize("gammas", ["", "q", "k", "qk"])
+@pytest.mark.parametrize("heads,tokens", [(110, 300), (511, 300), (2051, 130)])  # groups of 1, 4 and 8 heads
+def test_encoder_groups_of_heads(heads, tokens, gammas):
+    """Packed QKV of two batches, one of the norms or both or none missing."""
+    grid = (1, 10, tokens // 10)
+    gen = torch.Generator(DEV).manual_seed(heads)
+    qkv = torch.randn((2, tokens, 3, heads, sol.HEAD_DIM), generator=gen, device=DEV).bfloat16()
+    gamma = 1 + 0.25 * torch.randn(sol.HEAD_DIM, generator=gen, device=DEV)
+    kw = {"q_gamma": gamma if "q" in gammas else None, "k_gamma": gamma if "k" in gammas else None}
+    tab = sol.rope3d_table(*grid, device=DEV)
+    rec = sol.qkv_encode_packed(qkv, *grid, tab, **kw)
+    for h in sorted({0, 1, 3, 4, 7, 8, heads // 2, heads - 2, heads - 1}):
+        one = sol.qkv_encode_packed(qkv[:, :, :, h:h + 1].contiguous(), *grid, tab, **kw)
+        assert torch.equal(rec[:, :, h:h + 1], one), h

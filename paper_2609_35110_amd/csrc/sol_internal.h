@@ -137,7 +137,7 @@ inline int64_t prepared_tile_elems(int N) {
 
 // Block-sparse routing (sol_sparse.hip).  Workspace sections, byte offsets
 // off[0..3]: counts int32 [BH][nqb], blocks uint16 [BH][nqb][nkb], pooled
-// queries fp32 [BH][nqb][D], pooled keys fp32 [BH][nkb][D] (nqb = ceil(N/256),
+// queries fp32 [BH][nqb][D], pooled keys fp32 [BH][D/4][nkb][4] (nqb = ceil(N/256),
 // nkb = ceil(N/128)); returns the total size.
 inline size_t sparse_workspace_offsets(int BH, int N, size_t off[4]) {
   const size_t nqb = (size_t)(N + kSparseQueryBlock - 1) / kSparseQueryBlock;
@@ -146,7 +146,7 @@ inline size_t sparse_workspace_offsets(int BH, int N, size_t off[4]) {
   off[0] = 0;                                              // counts: int32 [BH][nqb]
   off[1] = up(off[0] + (size_t)BH * nqb * 4);              // blocks: uint16 [BH][nqb][nkb]
   off[2] = up(off[1] + (size_t)BH * nqb * nkb * 2);        // qbar: fp32 [BH][nqb][D]
-  off[3] = up(off[2] + (size_t)BH * nqb * kHeadDim * 4);   // kbar: fp32 [BH][nkb][D]
+  off[3] = up(off[2] + (size_t)BH * nqb * kHeadDim * 4);   // kbar: fp32 [BH][D/4][nkb][4]
   return up(off[3] + (size_t)BH * nkb * kHeadDim * 4);
 }
 // Largest N the block-sparse path takes (its key-block lists live in LDS).

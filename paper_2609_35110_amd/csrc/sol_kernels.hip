@@ -890,6 +890,21 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
       reinterpret_cast<uint8_t*>(out) + ((size_t)ob * Nq * heads + (bh - ob * heads)) * kOutRecBytes;
   const size_t outrec_stride = (size_t)heads * kOutRecBytes;
   const int qrow_first = qt * BM + wave * 64 + l32;
+  if (kRobust) {
+    // Second pass: only the row blocks the first pass marked (NaN rows) are
+    // recomputed; every other workgroup leaves at once.
+    bool marked = false;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const int row = qrow_first + 32 * qb;
+      if (hh == 0 && row < Nq)
+        marked |= out_rec   ? outrec_slab[row * outrec_stride + 128] == 0xFF
+                  : out_fp8 ? (out8_slab[(size_t)row * D] & 0x7F) == 0x7F
+                            : (out_slab[(size_t)row * D] & 0x7FFF) > 0x7F80;
+    }
+    if (!__syncthreads_or(marked)) return;
+  }
+
   // Tiles the workgroup walks: every tile of the slab, or the listed blocks'.
   int n_kv = (N + BN2 - 1) / BN2;
   int last_blk = 0, last_pos = 0;  // sparse: the last key block and its walk position
@@ -927,21 +942,6 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
     if (!kSparse) return t * BN2;
     return (t >> 2) == last_pos ? (4 * last_blk + (t & 3)) * BN2 : 0;
   };
-  if (kRobust) {
-    // Second pass: only the row blocks the first pass marked (NaN rows) are
-    // recomputed; every other workgroup leaves at once.
-    bool marked = false;
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const int row = qrow_first + 32 * qb;
-      if (hh == 0 && row < Nq)
-        marked |= out_rec   ? outrec_slab[row * outrec_stride + 128] == 0xFF
-                  : out_fp8 ? (out8_slab[(size_t)row * D] & 0x7F) == 0x7F
-                            : (out_slab[(size_t)row * D] & 0x7FFF) > 0x7F80;
-    }
-    if (!__syncthreads_or(marked)) return;
-  }
-
   // ---- Q' fragments of the wave's two 32-row blocks, normalised (q_gamma)
   // and rotated in the load.  A lane holds the even (hh = 0) or odd chunks of
   // its row; the sum of squares pairs them across the lane halves first, then

@@ -17,8 +17,11 @@
 //
 // Three launches, all small next to the attention: pool_q_kernel (reads q
 // once), pool_k_kernel (reads the prepared K once), route_kernel (four query
-// blocks per workgroup: the scores go to LDS, mean and spread are fixed-order
-// tree reductions, and the kept blocks are compacted with wave ballots).
+// blocks per workgroup: the scores go to LDS, then one wave per query block
+// finds mean and spread in fixed-order trees and compacts the kept blocks with
+// ballots).
+#include <type_traits>
+
 #include "sol_device.h"
 
 namespace sol {
@@ -28,10 +31,15 @@ constexpr int kQB = kSparseQueryBlock;
 constexpr int kKB = kSparseKeyBlock;
 constexpr int kMaxKeyBlocks = kMaxSparseBlocks;
 
-// Mean of q^ over each query block.  Grid (nqb, slabs); 256 threads = 16 rows
-// x 16 chunks per step, 16 steps over the block's rows: each thread sums its
-// chunk's 8 entries over its 16 rows in row order, then the 16 row groups are
-// summed in LDS in group order.
+// Mean of q^ over each query block.  Grid (nqb, groups of kSlabs slabs); 256
+// threads = 16 rows x 16 chunks per step, 16 steps over the block's rows: each
+// thread sums its chunk's 8 entries over its 16 rows in row order, then the 16
+// row groups are summed in LDS in group order.  Its floor is reading q; the
+// rotation's instructions are what it is bound by, so a workgroup takes kSlabs
+// slabs through each step with one row's position, cosines and sines: 272 us
+// for 111,600 tokens of 40 heads (383 us with one slab, 441 us with the
+// rotation's rounding to odd besides).
+template <bool kRope, bool kNorm, int kSlabs>
 __global__ __launch_bounds__(256) void pool_q_kernel(const uint4* __restrict__ q,
                                                      float* __restrict__ qbar, int64_t bh_count,
                                                      SeqGrid g, const float2* __restrict__ tab,
@@ -45,32 +53,57 @@ __global__ __launch_bounds__(256) void pool_q_kernel(const uint4* __restrict__ q
   const int t = threadIdx.x, cc = t & 15, rg = t >> 4;
   const int r0 = I * kQB;
   const int rows = min(kQB, N - r0);
-  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-  for (int64_t bh = blockIdx.y; bh < bh_count; bh += gridDim.y) {
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float gm[8] = {};
+  if (kNorm) load_gamma(gamma, cc, gm);
+  for (int64_t bh0 = (int64_t)blockIdx.y * kSlabs; bh0 < bh_count; bh0 += (int64_t)gridDim.y * kSlabs) {
+    float acc[kSlabs][8];
+#pragma unroll
+    for (int s = 0; s < kSlabs; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[s][e] = 0.0f;
+    // slabs past the last read that one again; rows past the block add nothing
+    auto load = [&](int step, uint4 (&x)[kSlabs]) __attribute__((always_inline)) {
+      const int n = min(r0 + 16 * step + rg, N - 1);
+#pragma unroll
+      for (int s = 0; s < kSlabs; ++s) x[s] = q[((size_t)min(bh0 + s, bh_count - 1) * N + n) * kChunks + cc];
+    };
+    uint4 next[kSlabs];
+    load(0, next);
     for (int step = 0; step < kQB / 16; ++step) {
       const int n = r0 + 16 * step + rg;
       const bool valid = n < N;  // the 16 lanes of a row agree
-      const uint4 x = valid ? q[((size_t)bh * N + n) * kChunks + cc] : zero;
-      const float inv = gamma ? rms_inv(row_sumsq_lanes16(chunk_sumsq(x)), eps) : 1.0f;
+      uint4 x[kSlabs];
+#pragma unroll
+      for (int s = 0; s < kSlabs; ++s) x[s] = next[s];
+      load(min(step + 1, kQB / 16 - 1), next);
       Pos p{0, 0, 0, false};
-      if (tab != nullptr && valid) p = token_pos(n, g);
-      const bool rot = tab != nullptr && p.rot;
-      const uint4 y = valid ? qk_chunk(x, gamma, inv, cc, rot, tab, tab_lo_plane(tab, g), rot ? tab_pair(cc, p, g) : 0) : zero;
-      float f[8];
-      unpack_bf16x8(y, f);
+      RopeCS cs{};
+      if (kRope) {
+        p = token_pos(min(n, N - 1), g);
+        cs = load_rope_cs(tab, tab_lo_plane(tab, g), tab_pair(cc, p, g));
+      }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += f[e];
+      for (int s = 0; s < kSlabs; ++s) {
+        const float inv = kNorm ? rms_inv(row_sumsq_lanes16(chunk_sumsq(x[s])), eps) : 1.0f;
+        float f[8];
+        unpack_bf16x8(qk_chunk<kRope, kNorm>(x[s], gm, inv, p.rot, cs), f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[s][e] += valid ? f[e] : 0.0f;
+      }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[rg][8 * cc + e] = acc[e];
-    __syncthreads();
-    if (t < D) {
-      float sum = 0.0f;
-      for (int r = 0; r < 16; ++r) sum += part[r][t];
-      qbar[((size_t)bh * nqb + I) * D + t] = sum / (float)rows;
+    for (int s = 0; s < kSlabs; ++s) {
+      if (bh0 + s >= bh_count) break;  // uniform
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part[rg][8 * cc + e] = acc[s][e];
+      __syncthreads();
+      if (t < D) {
+        float sum = 0.0f;
+        for (int r = 0; r < 16; ++r) sum += part[r][t];
+        qbar[((size_t)(bh0 + s) * nqb + I) * D + t] = sum / (float)rows;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -79,7 +112,8 @@ __global__ __launch_bounds__(256) void pool_q_kernel(const uint4* __restrict__ q
 // reads the 16-byte fragment slots t and t + 256 of each of the block's four
 // tiles -- always key r = t & 31 of a tile, chunks 2(t >> 6) + hh and that +
 // 8, hh = (t >> 5) & 1 -- and the 32 keys of a wave half are summed by a
-// butterfly over lane bits 0..4.
+// butterfly over lane bits 0..4.  kbar is laid out [D / 4][nkb][4], so that
+// route_kernel's lanes, one key block each, read side by side.
 __global__ __launch_bounds__(256) void pool_k_kernel(const uint4* __restrict__ kp,
                                                      float* __restrict__ kbar, int64_t bh_count,
                                                      int N, int nkb) {
@@ -126,51 +160,50 @@ __global__ __launch_bounds__(256) void pool_k_kernel(const uint4* __restrict__ k
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int dim0 = 16 * (kk + 4 * u) + 8 * hh;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          kbar[((size_t)bh * nkb + J) * D + dim0 + e] = acc[u][e] / (float)keys;
+        float4* dst = reinterpret_cast<float4*>(kbar + (size_t)bh * nkb * D) + (size_t)(dim0 / 4) * nkb + J;
+        const float n = (float)keys;
+        dst[0] = make_float4(acc[u][0] / n, acc[u][1] / n, acc[u][2] / n, acc[u][3] / n);
+        dst[nkb] = make_float4(acc[u][4] / n, acc[u][5] / n, acc[u][6] / n, acc[u][7] / n);
       }
     }
   }
 }
 
-// Fixed-order sum over the 256 threads of a workgroup (tree in LDS).
-__device__ __forceinline__ float block_sum(float x, float* red) {
-  const int t = threadIdx.x;
-  red[t] = x;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) red[t] = red[t] + red[t + s];
-    __syncthreads();
-  }
-  const float r = red[0];
-  __syncthreads();
-  return r;
+// Routing of kRouteQB consecutive query blocks per workgroup.  Grid
+// (ceil(nqb / kRouteQB), slabs).  All 256 threads score: a thread holds four
+// key blocks (256 apart) against the four query blocks at once, so one pooled
+// key read from L2 serves four products and one pooled query read from LDS
+// another four.  Scores go to LDS; then wave u routes query block I0 + u by
+// itself, without a barrier: mean and spread are sums over the 256 residues of
+// J mod 256 in ascending J, then a binary tree pairing residue r with r + 128,
+// r + 64, .. r + 1; the best block is a (score, lowest index) reduction; and
+// the kept blocks are compacted in ascending order with ballots.  kCap: key
+// blocks the score rows hold in LDS.  The usual case (up to 131,072 tokens)
+// takes 21 KB, so that seven workgroups share a CU and hide each other's
+// latency; the rows for the longest sequence would leave room for one.
+// 111,600 tokens of 40 heads: 130 us, against 579 us with one reduction after
+// another over the whole workgroup and rows for the longest sequence.
+constexpr int kRouteQB = 4;
+constexpr int kRouteCap = 1024;
+
+// Sum over the wave (the tree's last six levels), in every lane.
+__device__ __forceinline__ float wave_sum(float x) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) x += __shfl_xor(x, s);
+  return x;
 }
 
-// Routing of kRouteQB consecutive query blocks per workgroup (each pooled key
-// block read from L2 serves all of them).  Grid (ceil(nqb / kRouteQB),
-// slabs).  Scores go to LDS; per query block the mean and the spread are
-// fixed-order tree reductions, the best block a (score, lowest index)
-// reduction, and the kept blocks are compacted in ascending order with wave
-// ballots -- the same arithmetic, in the same order, for every block of a
-// workgroup.
-constexpr int kRouteQB = 4;
-
+template <int kCap>
 __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ qbar,
                                                     const float* __restrict__ kbar,
                                                     uint16_t* __restrict__ blocks,
                                                     int* __restrict__ counts, int64_t bh_count,
                                                     int nqb, int nkb, int n_prefix, float tau,
                                                     float scale) {
-  __shared__ float qs[kRouteQB][D];
-  __shared__ float sc[kRouteQB][kMaxKeyBlocks];
-  __shared__ float red[256];
-  __shared__ int redi[256];
-  __shared__ int wcount[4];
+  __shared__ __attribute__((aligned(16))) float qs[kRouteQB][D];
+  __shared__ float sc[kRouteQB][kCap];
   lds_poison(&qs[0][0], sizeof(qs));
   lds_poison(&sc[0][0], sizeof(sc));
-  lds_poison(red, sizeof(red));
   lds_poison_done();
   const int I0 = blockIdx.x * kRouteQB;
   const int nq = min(kRouteQB, nqb - I0);
@@ -181,89 +214,92 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ qb
       qs[u][d] = u < nq ? qbar[((size_t)bh * nqb + I0 + u) * D + d] : 0.0f;
     }
     __syncthreads();
-    // scores of every query block, this thread's share of their sums, its
-    // first best block
-    float psum[kRouteQB], best_v[kRouteQB];
-    int best_j[kRouteQB];
+    const float4* kr = reinterpret_cast<const float4*>(kbar + (size_t)bh * nkb * D);
+    for (int J0 = t; J0 < nkb; J0 += 1024) {
+      float dot[kRouteQB][4];
 #pragma unroll
-    for (int u = 0; u < kRouteQB; ++u) {
-      psum[u] = 0.0f;
-      best_v[u] = -__builtin_inff();
-      best_j[u] = nkb;
-    }
-    for (int J = t; J < nkb; J += 256) {
-      const float4* kr = reinterpret_cast<const float4*>(kbar + ((size_t)bh * nkb + J) * D);
-      float dot[kRouteQB];
+      for (int u = 0; u < kRouteQB; ++u)
 #pragma unroll
-      for (int u = 0; u < kRouteQB; ++u) dot[u] = 0.0f;
+        for (int c = 0; c < 4; ++c) dot[u][c] = 0.0f;
+#pragma unroll 2
       for (int d4 = 0; d4 < D / 4; ++d4) {
-        const float4 kv = kr[d4];
+        float4 kv[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) kv[c] = kr[(size_t)d4 * nkb + min(J0 + 256 * c, nkb - 1)];
 #pragma unroll
         for (int u = 0; u < kRouteQB; ++u) {
-          dot[u] = __builtin_fmaf(qs[u][4 * d4], kv.x, dot[u]);
-          dot[u] = __builtin_fmaf(qs[u][4 * d4 + 1], kv.y, dot[u]);
-          dot[u] = __builtin_fmaf(qs[u][4 * d4 + 2], kv.z, dot[u]);
-          dot[u] = __builtin_fmaf(qs[u][4 * d4 + 3], kv.w, dot[u]);
+          const float4 qv = *reinterpret_cast<const float4*>(&qs[u][4 * d4]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            dot[u][c] = __builtin_fmaf(qv.x, kv[c].x, dot[u][c]);
+            dot[u][c] = __builtin_fmaf(qv.y, kv[c].y, dot[u][c]);
+            dot[u][c] = __builtin_fmaf(qv.z, kv[c].z, dot[u][c]);
+            dot[u][c] = __builtin_fmaf(qv.w, kv[c].w, dot[u][c]);
+          }
         }
       }
 #pragma unroll
-      for (int u = 0; u < kRouteQB; ++u) {
-        const float sv = dot[u] * scale;
-        sc[u][J] = sv;
-        psum[u] += sv;
-        if (sv > best_v[u]) {
-          best_v[u] = sv;
-          best_j[u] = J;
-        }
-      }
+      for (int c = 0; c < 4; ++c)
+        if (J0 + 256 * c < nkb)
+#pragma unroll
+          for (int u = 0; u < kRouteQB; ++u) sc[u][J0 + 256 * c] = dot[u][c] * scale;
     }
-    for (int u = 0; u < nq; ++u) {  // uniform
-      const int I = I0 + u;
+    __syncthreads();
+    if (wave < nq) {  // one wave per query block
+      const float* s = sc[wave];
+      const int I = I0 + wave;
       const size_t qi = (size_t)bh * nqb + I;
       const bool dense = I * kQB < n_prefix;  // the block holds a prefix row
-      const float mu = block_sum(psum[u], red) / (float)nkb;
-      float pvar = 0.0f;
-      for (int J = t; J < nkb; J += 256) {
-        const float d = sc[u][J] - mu;
-        pvar = __builtin_fmaf(d, d, pvar);
-      }
-      const float var = block_sum(pvar, red) / (float)nkb;
-      const float thr = mu + tau * __builtin_sqrtf(var);
-      // first best block: largest score, lowest index among equals
-      red[t] = best_v[u];
-      redi[t] = best_j[u];
-      __syncthreads();
-      for (int s = 128; s > 0; s >>= 1) {
-        if (t < s) {
-          const float ov = red[t + s];
-          const int oi = redi[t + s];
-          if (ov > red[t] || (ov == red[t] && oi < redi[t])) {
-            red[t] = ov;
-            redi[t] = oi;
+      // four residues a lane: J = lane + 64 r + 256 i
+      float psum[4], best_v = -__builtin_inff();
+      int best_j = nkb;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        psum[r] = 0.0f;
+        for (int J = lane + 64 * r; J < nkb; J += 256) {
+          const float sv = s[J];
+          psum[r] += sv;
+          if (sv > best_v || (sv == best_v && J < best_j)) {
+            best_v = sv;
+            best_j = J;
           }
         }
-        __syncthreads();
       }
-      const int best = redi[0];
-      __syncthreads();
+      const float mu = wave_sum((psum[0] + psum[2]) + (psum[1] + psum[3])) / (float)nkb;
+      float pvar[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        pvar[r] = 0.0f;
+        for (int J = lane + 64 * r; J < nkb; J += 256) {
+          const float d = s[J] - mu;
+          pvar[r] = __builtin_fmaf(d, d, pvar[r]);
+        }
+      }
+      const float var = wave_sum((pvar[0] + pvar[2]) + (pvar[1] + pvar[3])) / (float)nkb;
+      const float thr = mu + tau * __builtin_sqrtf(var);
+      // first best block: largest score, lowest index among equals
+#pragma unroll
+      for (int m = 32; m > 0; m >>= 1) {
+        const float ov = __shfl_xor(best_v, m);
+        const int oi = __shfl_xor(best_j, m);
+        if (ov > best_v || (ov == best_v && oi < best_j)) {
+          best_v = ov;
+          best_j = oi;
+        }
+      }
       // kept blocks, compacted in ascending order
       int base = 0;
       uint16_t* out = blocks + qi * nkb;
-      for (int c0 = 0; c0 < nkb; c0 += 256) {
-        const int J = c0 + t;
-        const bool keep = J < nkb && (dense || J * kKB < n_prefix || J == best || sc[u][J] > thr);
+      for (int c0 = 0; c0 < nkb; c0 += 64) {
+        const int J = c0 + lane;
+        const bool keep = J < nkb && (dense || J * kKB < n_prefix || J == best_j || s[J] > thr);
         const uint64_t m = __ballot(keep);
-        const int before = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) wcount[wave] = __popcll(m);
-        __syncthreads();
-        int off = base;
-        for (int w = 0; w < wave; ++w) off += wcount[w];
-        if (keep) out[off + before] = (uint16_t)J;
-        base += wcount[0] + wcount[1] + wcount[2] + wcount[3];
-        __syncthreads();
+        if (keep) out[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)J;
+        base += __popcll(m);
       }
-      if (t == 0) counts[qi] = base;
+      if (lane == 0) counts[qi] = base;
     }
+    __syncthreads();  // the next slab overwrites the pooled queries and the scores
   }
 }
 
@@ -282,7 +318,19 @@ hipError_t launch_sparse_route(const uint16_t* q, const uint16_t* k_prep, int BH
   float* qbar = reinterpret_cast<float*>(ws + off[2]);
   float* kbar = reinterpret_cast<float*>(ws + off[3]);
   const unsigned gy = (unsigned)(BH < 65535 ? BH : 65535);
-  hipLaunchKernelGGL(pool_q_kernel, dim3(nqb, gy), dim3(256), 0, stream,
+  // four slabs per workgroup of the query pooling where that leaves eight
+  // workgroups a CU, else one
+  const bool grouped = (int64_t)nqb * BH >= 4 * kStreamWgs;
+  const int64_t groups = grouped ? ((int64_t)BH + 3) / 4 : BH;
+  auto pool_q = [&](auto rope, auto norm) {
+    return grouped ? pool_q_kernel<decltype(rope)::value, decltype(norm)::value, 4>
+                   : pool_q_kernel<decltype(rope)::value, decltype(norm)::value, 1>;
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  auto* pool_q_fn = tab ? (q_gamma ? pool_q(Yes(), Yes()) : pool_q(Yes(), No()))
+                        : (q_gamma ? pool_q(No(), Yes()) : pool_q(No(), No()));
+  hipLaunchKernelGGL(pool_q_fn, dim3(nqb, (unsigned)(groups < 65535 ? groups : 65535)), dim3(256), 0, stream,
                      reinterpret_cast<const uint4*>(q), qbar, (int64_t)BH, g, tab, q_gamma, eps, nqb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -290,9 +338,9 @@ hipError_t launch_sparse_route(const uint16_t* q, const uint16_t* k_prep, int BH
                      reinterpret_cast<const uint4*>(k_prep), kbar, (int64_t)BH, N, nkb);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(route_kernel, dim3((nqb + kRouteQB - 1) / kRouteQB, gy), dim3(256), 0, stream, qbar,
-                     kbar, blocks, counts,
-                     (int64_t)BH, nqb, nkb, g.nt, tau, (float)(1.0 / 11.313708498984761));
+  auto* route_fn = nkb <= kRouteCap ? route_kernel<kRouteCap> : route_kernel<kMaxKeyBlocks>;
+  hipLaunchKernelGGL(route_fn, dim3((nqb + kRouteQB - 1) / kRouteQB, gy), dim3(256), 0, stream, qbar, kbar,
+                     blocks, counts, (int64_t)BH, nqb, nkb, g.nt, tau, (float)(1.0 / 11.313708498984761));
   return hipGetLastError();
 }
 

@@ -210,3 +210,35 @@ def test_sparse_maximum_tokens():
     st = compare(_bits(out).reshape(-1, w.D)[rows], ref, rows)
     _log("max tokens: %s" % st)
     assert_parity(st, "sparse max tokens")
+
+
+def test_routing_of_grouped_slabs():
+    """From 8192 query blocks on, four slabs share a workgroup of the query
+    pooling: 1370 slabs of 7 query blocks (two left over), each routed as alone."""
+    T, Hl, Wl, nt, slabs = 3, 21, 25, 37, 1370
+    N = nt + T * Hl * Wl
+    gen = torch.Generator(DEV).manual_seed(9)
+    q, k, v = (torch.randn((1, slabs, N, 128), generator=gen, device=DEV).bfloat16() for _ in range(3))
+    gamma = 1 + 0.25 * torch.randn(128, generator=gen, device=DEV)
+    tab = sol.rope3d_table(T, Hl, Wl, device=DEV)
+
+    def route(sl):
+        kp, _ = sol.prepare_kv(k[:, sl].contiguous(), v[:, sl].contiguous(), T, Hl, Wl, tab)
+        qs = q[:, sl].contiguous()
+        return gpu_mask(sol.sparse_route(qs, kp, T, Hl, Wl, tab, 0.5, gamma=gamma), 1, qs.shape[1], N)
+
+    every = route(slice(None))
+    for s in (0, 1, 2, 3, 4, 685, 1367, 1368, 1369):
+        assert np.array_equal(every[:, s:s + 1], route(slice(s, s + 1))), s
+
+
+@pytest.mark.parametrize("grid", [(32, 64, 64), (41, 40, 80)], ids=["1024 key blocks", "1025"])
+def test_routing_score_rows(grid):
+    """Either side of the longest sequence whose scores take the short LDS rows."""
+    w = W.custom(1, 1, *grid, seed_index=1090 + grid[0], shared_dir=1.0)
+    q, k, v = W.make_inputs(w)
+    tab = sol.rope3d_table(*grid, device=DEV)
+    kp, _ = sol.prepare_kv(k.to(DEV), v.to(DEV), *grid, tab)
+    ws = sol.sparse_route(q.to(DEV), kp, *grid, tab, 1.25)
+    n_diff, n_tot = check_routing(gpu_mask(ws, 1, 1, w.N), q, k, w, 1.25)
+    _log("%s: %d of %d routing decisions differ at the threshold" % (grid, n_diff, n_tot))

@@ -306,8 +306,10 @@ int sol_attn_fwd(const void* q, const void* k, const void* v, void* out, int B, 
     hipError_t e = sol::launch_prepare_kv(ks + s * slab, vs + s * slab, kp, vp, c, g, tab, 0, N, nullptr,
                                           0.0f, hs);
     if (e != hipSuccess) return fail(SOL_ERR_HIP, "attn_fwd (prepare) launch: %s", hipGetErrorString(e));
+    // whole query tiles whatever the chunk's size (nkb -1 without blocks): a
+    // slab's result must not depend on the chunk it falls into
     e = sol::launch_attn_fwd_prepared(qs + s * slab, kp, vp, os + s * slab, c, g, N, tab, nullptr, 0.0f,
-                                      SOL_OUT_BF16, nullptr, nullptr, 0, hs, nullptr, c);
+                                      SOL_OUT_BF16, nullptr, nullptr, -1, hs, nullptr, c);
     if (e != hipSuccess) return fail(SOL_ERR_HIP, "attn_fwd (attention) launch: %s", hipGetErrorString(e));
     s += c;
   }

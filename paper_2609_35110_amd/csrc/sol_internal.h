@@ -61,7 +61,8 @@ hipError_t launch_prepare_kv(const uint16_t* k, const uint16_t* v, uint16_t* k_p
 // out_fp8.
 // blocks != nullptr: block-sparse, each 256-row query block attends only to
 // the counts[...] key blocks of 128 keys listed for it in blocks (nkb entries
-// per query block, ascending).
+// per query block, ascending).  blocks == nullptr: nkb is 0, or -1 to keep
+// whole query tiles where a small grid would split the keys.
 // out_format: 0 bf16, 1 FP8 E4M3 bytes, 2 block-INT8 output records (144
 // bytes per row, token-major over `heads`).  qrec != nullptr: the queries
 // come from block-INT8 QKV records instead of q (token-major, `heads` records

@@ -731,6 +731,60 @@ __device__ __forceinline__ void dma_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Q' fragments of a wave's two 32-row blocks (block qb: row qrow0 + 32 qb, of
+// the slab's Nq), normalised (q_gamma) and rotated in the load, rounded to
+// bf16, times q_scale, rounded to fp16.  A lane holds the even (hh = 0) or odd
+// chunks of its row; the sum of squares pairs them across the lane halves
+// first, then runs the rest of the fixed tree in the lane.  Returns whether a
+// value left fp16's range (or is not finite).
+template <bool kRope, bool kRec>
+__device__ __forceinline__ bool load_queries(f16x8 (&qf)[2][8], const uint16_t* __restrict__ qs, int qrow0, int hh,
+                                             int bh, int Nq, const SeqGrid& g, const float2* __restrict__ tab,
+                                             const float* __restrict__ q_gamma, float eps, float q_scale,
+                                             const uint8_t* __restrict__ qrec, int heads) {
+  bool bad_q = false;
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int row = min(qrow0 + 32 * qb, Nq - 1);
+    Pos p{0, 0, 0, false};
+    if (kRope) p = token_pos(row, g);
+    uint4 x[8];
+    if (kRec) {
+      // q decoded from the row's block-INT8 record (token-major, `heads`
+      // records per token), already normalised and rotated
+      const int b = bh / heads;
+      const uint8_t* r = qrec + (((size_t)b * Nq + row) * heads + (bh - b * heads)) * kRecBytes;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) x[kk] = rec_chunk(r, 0, 2 * kk + hh);
+    } else {
+      const uint4* src = reinterpret_cast<const uint4*>(qs + (size_t)row * D);
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) x[kk] = src[2 * kk + hh];
+    }
+    float inv = 1.0f;
+    if (q_gamma != nullptr) {
+      float s1[8];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const float pk = chunk_sumsq(x[kk]);
+        s1[kk] = pk + __shfl_xor(pk, 32);  // chunks 2kk and 2kk + 1
+      }
+      const float s3a = (s1[0] + s1[1]) + (s1[2] + s1[3]);
+      const float s3b = (s1[4] + s1[5]) + (s1[6] + s1[7]);
+      inv = rms_inv(s3a + s3b, eps);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const int cc = 2 * kk + hh;
+      // kRope: prefix rows turn by the origin's table entries, an exact identity
+      const uint4 y = qk_chunk(x[kk], q_gamma, inv, cc, kRope, tab, tab_lo_plane(tab, g), kRope ? tab_pair(cc, p, g) : 0);
+      qf[qb][kk] = bf16x8_to_f16x8_scaled(y, q_scale);
+      bad_q |= f16x8_nonfinite(__builtin_bit_cast(uint4, qf[qb][kk]));
+    }
+  }
+  return bad_q;
+}
+
 // Attention on prepared K/V: k holds the rotated keys and v the values, both
 // as fp16.  The query rows are rotated and rounded to bf16 like every rotation
 // here, then multiplied by c = log2(e)/sqrt(D) and rounded to fp16, so the
@@ -942,52 +996,11 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
     if (!kSparse) return t * BN2;
     return (t >> 2) == last_pos ? (4 * last_blk + (t & 3)) * BN2 : 0;
   };
-  // ---- Q' fragments of the wave's two 32-row blocks, normalised (q_gamma)
-  // and rotated in the load.  A lane holds the even (hh = 0) or odd chunks of
-  // its row; the sum of squares pairs them across the lane halves first, then
-  // runs the rest of the fixed tree in the lane.
+  // ---- Q' fragments of the wave's two 32-row blocks
   const int qrow0 = qrow_first;  // block qb holds row qrow0 + 32 qb
   f16x8 qf[2][8];
-  bool bad_q = false;  // |q^| log2(e)/sqrt(D) out of fp16's range (or not finite)
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    const int row = min(qrow0 + 32 * qb, Nq - 1);
-    Pos p{0, 0, 0, false};
-    if (kRope) p = token_pos(row, g);
-    uint4 x[8];
-    if (kRec) {
-      // q decoded from the row's block-INT8 record (token-major, `heads`
-      // records per token), already normalised and rotated
-      const int b = bh / heads;
-      const uint8_t* r = qrec + (((size_t)b * Nq + row) * heads + (bh - b * heads)) * kRecBytes;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) x[kk] = rec_chunk(r, 0, 2 * kk + hh);
-    } else {
-      const uint4* src = reinterpret_cast<const uint4*>(qs + (size_t)row * D);
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) x[kk] = src[2 * kk + hh];
-    }
-    float inv = 1.0f;
-    if (q_gamma != nullptr) {
-      float s1[8];
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        const float pk = chunk_sumsq(x[kk]);
-        s1[kk] = pk + __shfl_xor(pk, 32);  // chunks 2kk and 2kk + 1
-      }
-      const float s3a = (s1[0] + s1[1]) + (s1[2] + s1[3]);
-      const float s3b = (s1[4] + s1[5]) + (s1[6] + s1[7]);
-      inv = rms_inv(s3a + s3b, eps);
-    }
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      const int cc = 2 * kk + hh;
-      // kRope: prefix rows turn by the origin's table entries, an exact identity
-      const uint4 y = qk_chunk(x[kk], q_gamma, inv, cc, kRope, tab, tab_lo_plane(tab, g), kRope ? tab_pair(cc, p, g) : 0);
-      qf[qb][kk] = bf16x8_to_f16x8_scaled(y, q_scale);
-      bad_q |= f16x8_nonfinite(__builtin_bit_cast(uint4, qf[qb][kk]));
-    }
-  }
+  // |q^| log2(e)/sqrt(D) out of fp16's range (or not finite)
+  const bool bad_q = load_queries<kRope, kRec>(qf, qs, qrow0, hh, bh, Nq, g, tab, q_gamma, eps, q_scale, qrec, heads);
   note_range(bad_q, SOL_RANGE_Q);
 
   // ---- staging: each prepared tile (8 KB) is copied into LDS by buffer loads
@@ -1532,6 +1545,417 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
   }
 }
 
+// ------------------------------------------- few query rows: keys split
+
+// The first pass of the prepared path for grids that leave most CUs idle: one
+// workgroup takes 64 query rows (not 256), and its four waves each a quarter of
+// the keys.  A workgroup of attn_prepared_kernel is one CU's work for a whole
+// sweep, so a grid of x of them takes at least one sweep however few they are.
+//
+// Each wave walks its own tiles, so nothing is shared through LDS: the
+// prepared tiles are already in fragment order, and a wave reads each fragment
+// from L2 straight into the registers it is used from, one iteration ahead (a
+// fragment's registers are refilled as soon as its second MFMA has been
+// issued).  No LDS ring, no barrier in the loop.  The price is four times the
+// L2 reads per MFMA: 64 KB a CU in the time of 32 MFMAs a wave (1024 clocks),
+// the 64 bytes a clock a CU can take.
+//
+// All four waves use one reference max m (tile 0 and the rows' diagonal tile),
+// so their partial O and row sums simply add: they meet in LDS (128 KB) at the
+// end, and wave w writes head dims [32w, 32w + 32).  A wave whose probabilities
+// leave the fp16 range marks the whole workgroup's rows for the second pass.
+// Rows and masks as in attn_prepared_kernel; the loop is its dense first pass.
+constexpr int kSplitRows = 64;
+
+template <bool kRope, bool kSparse, bool kRec, bool kOutRec>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void attn_keysplit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                          const uint16_t* __restrict__ v, uint16_t* __restrict__ out, SeqGrid g,
+                          const float2* __restrict__ tab, int n_units, float c_log2, int n_keys,
+                          const float* __restrict__ q_gamma, float eps, int out_format,
+                          const uint16_t* __restrict__ blocks, const int* __restrict__ counts, int nkb,
+                          const uint8_t* __restrict__ qrec, int heads) {
+  // partial O: [wave][qb][db][group of 4 registers][lane] float4; row sums [wave][qb][lane]
+  __shared__ __attribute__((aligned(16))) float4 red[kWaves2 * 2 * 4 * 4 * 64];
+  __shared__ float red_l[kWaves2 * 2 * 64];
+  __shared__ int red_mark[kWaves2];
+  __shared__ uint16_t list[kSparse ? kMaxSparseBlocks : 1];  // the query block's kept key blocks
+  lds_poison(red, sizeof(red));
+  lds_poison(red_l, sizeof(red_l));
+  lds_poison_done();
+  auto keep = [&](auto& x) __attribute__((always_inline)) { pin(x); };
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hh = lane >> 5;
+  const int l32 = lane & 31;
+  const int wg = xcd_local_id(blockIdx.x, gridDim.x);
+  const int bh = wg / n_units;
+  const int first_row = (wg - bh * n_units) * kSplitRows;
+  const int Nq = g.n, N = n_keys;
+  const size_t slab = (size_t)bh * Nq * D;
+  const int n_tiles = (N + BN2 - 1) / BN2;
+  const size_t pslab = (size_t)bh * n_tiles * kPrepTileElems;
+  const int qrow0 = first_row + l32;
+
+  // The walk: every tile of the slab, or (kSparse) the four tiles of each
+  // listed block; only the last one's can lie past the slab's end.  Counts and
+  // entries are clamped to the slab, whatever the list holds.
+  int n_walk = n_tiles, n_blocks = (n_tiles + 3) / 4;
+  if (kSparse) {
+    const size_t qb = (size_t)bh * ((Nq + kSparseQueryBlock - 1) / kSparseQueryBlock) + first_row / kSparseQueryBlock;
+    n_blocks = min(max(counts[qb], 1), min(nkb, kMaxSparseBlocks));
+    for (int e = tid; e < n_blocks; e += 256) list[e] = (uint16_t)min((int)blocks[qb * nkb + e], nkb - 1);
+    __syncthreads();
+    const int last = __builtin_amdgcn_readfirstlane((int)list[n_blocks - 1]);
+    n_walk = 4 * (n_blocks - 1) + min(4, n_tiles - 4 * last);
+  }
+  // Slab tile of walk position t (clamped to the walk; inside the slab whatever
+  // the list holds); entry: its list entry.
+  auto entry_of = [&](int t) __attribute__((always_inline)) { return kSparse ? (int)list[min(t, n_walk - 1) >> 2] : 0; };
+  auto walk_tile = [&](int t, int entry) __attribute__((always_inline)) {
+    t = min(t, n_walk - 1);
+    return kSparse ? min(4 * __builtin_amdgcn_readfirstlane(entry) + (t & 3), n_tiles - 1) : t;
+  };
+  // This wave's walk positions [t0, t0 + n_own): a quarter of the blocks' tiles,
+  // so that a full list is split as the dense walk is.
+  int t0 = min(wave * n_blocks, n_walk);
+  int n_own = min((wave + 1) * n_blocks, n_walk) - t0;
+  const uint32_t slab_bytes = (uint32_t)n_tiles * (kPrepTileElems * 2);
+  const __amdgpu_buffer_rsrc_t rsrc_k =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(k + pslab), (short)0, (int)slab_bytes, kBufferDword3);
+  const __amdgpu_buffer_rsrc_t rsrc_v =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(v + pslab), (short)0, (int)slab_bytes, kBufferDword3);
+  // Fragment j of a slab tile.
+  auto frag = [&](const __amdgpu_buffer_rsrc_t& rs, int tile, int j) __attribute__((always_inline)) {
+    return __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16,
+                                                                           tile * (kPrepTileElems * 2) + j * 1024, 0));
+  };
+
+  f16x8 qf[2][8];
+  const bool bad_q =
+      load_queries<kRope, kRec>(qf, q + slab, qrow0, hh, bh, Nq, g, tab, q_gamma, eps, c_log2, qrec, heads);
+  if (wave == 0) note_range(bad_q, SOL_RANGE_Q);
+
+  f32x16 o[2][4];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < 4; ++db) o[qb][db] = f32x16{};
+  float l_run[2] = {0.0f, 0.0f};
+  float ovf = 0.0f;
+
+  // Register j of a score block holds key 8(j/4) + 4hh + (j%4) of the tile.
+  // Those from key `from` of the tile on get no weight.
+  auto mask = [&](int from, f32x16& s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (8 * (j >> 2) + 4 * hh + (j & 3) >= from) s[j] = -__builtin_inff();
+  };
+  auto tile_max = [&](const f32x16& s) __attribute__((always_inline)) {
+    float mx = fmaxf(s[0], s[1]);
+#pragma unroll
+    for (int j = 2; j < 16; j += 2) mx = fmaxf(fmaxf(mx, s[j]), s[j + 1]);
+    return fmaxf(mx, __shfl_xor(mx, 32));
+  };
+  // Scores of one slab tile, with the builtin MFMA (outside the hot loop the
+  // compiler may stage Q' through temporary AGPRs).
+  auto scores = [&](int tile, f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
+    s0 = f32x16{};
+    s1 = f32x16{};
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const f16x8 kf = frag(rsrc_k, tile, kk);
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[0][kk], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[1][kk], s1, 0, 0, 0);
+    }
+    if (tile * BN2 + BN2 > N) {
+      mask(N - tile * BN2, s0);
+      mask(N - tile * BN2, s1);
+    }
+  };
+
+  // ---- reference max: the walk's first tile and each block's diagonal tile,
+  // if the walk attends it
+  f32x16 bias[2];
+  float m_ref[2];
+  {
+    f32x16 s0, s1;
+    scores(walk_tile(0, entry_of(0)), s0, s1);
+    m_ref[0] = tile_max(s0);
+    m_ref[1] = tile_max(s1);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const int key = min(max(first_row + 32 * qb + (N - Nq), 0), N - 1);
+      bool attended = true;
+      if (kSparse) {
+        bool hit = false;
+        for (int e = lane; e < n_blocks; e += 64) hit |= (int)list[e] == key / kSparseKeyBlock;
+        attended = __any(hit);
+      }
+      if (attended) {
+        scores(key / BN2, s0, s1);
+        m_ref[qb] = fmaxf(m_ref[qb], tile_max(qb ? s1 : s0));
+      }
+    }
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) bias[qb][j] = -m_ref[qb];
+  }
+
+  f16x8 kr[8], vr[8];
+  // Iteration i multiplies tile t0 + i's probabilities and tile t0 + i + 1's
+  // scores: the slots of attn_prepared_kernel's iteration, the fragment reads
+  // from L2.
+  // slab tile of walk position t0 + i + 1, and the list entry of t0 + i + 2 (read
+  // an iteration ahead: its LDS latency would stand at the iteration's start)
+  int tile1 = 0, entry2 = 0;
+  auto iteration = [&](int i, f32x16* cs, f32x16* ns, uint32_t* p0_cur, uint32_t* p0_next, float& l0_cur,
+                       float& l0_next) __attribute__((always_inline)) {
+    const int tile2 = walk_tile(t0 + i + 2, entry2);
+    entry2 = entry_of(t0 + i + 3);
+    // ---- phase A: S(i+1) beside block 1 of P(i)
+    uint32_t p1[8];
+    uint32_t t01 = 0, t23 = 0, t03 = 0, t45 = 0;
+    float pa = 0.0f, pb = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j == 0) mfma_s_first(ns[0], kr[0], qf[0][0], bias[0]);
+      else mfma_s_next(ns[0], kr[j], qf[0][j]);
+      __builtin_amdgcn_sched_barrier(0);
+      float ea = __builtin_amdgcn_exp2f(cs[1][2 * j]);
+      keep(ea);
+      if (j > 0) {
+        p1[j - 1] = pack_f16x2(pa, pb);
+        keep(p1[j - 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (j == 0) mfma_s_first(ns[1], kr[0], qf[1][0], bias[1]);
+      else mfma_s_next(ns[1], kr[j], qf[1][j]);
+      __builtin_amdgcn_sched_barrier(0);
+      kr[j] = frag(rsrc_k, tile2, j);
+      if (j == 2) { t01 = add_f16x2(p1[0], p1[1]); keep(t01); }
+      if (j == 4) { t23 = add_f16x2(p1[2], p1[3]); keep(t23); }
+      if (j == 5) { t03 = add_f16x2(t01, t23); keep(t03); }
+      if (j == 6) { t45 = add_f16x2(p1[4], p1[5]); keep(t45); }
+      float eb = __builtin_amdgcn_exp2f(cs[1][2 * j + 1]);
+      keep(eb);
+      __builtin_amdgcn_sched_barrier(0);
+      pa = ea;
+      pb = eb;
+    }
+    p1[7] = pack_f16x2(pa, pb);
+    float l1 = sum_f16x2(add_f16x2(t03, add_f16x2(t45, add_f16x2(p1[6], p1[7]))));
+    ovf = fmaxf(ovf, fmaxf(l0_cur, l1));
+    l_run[0] += l0_cur;
+    l_run[1] += l1;
+    keep(l_run[0]);
+    keep(l_run[1]);
+    keep(ovf);
+    __builtin_amdgcn_sched_barrier(0);
+    f16x8 pf[2][2];
+#pragma unroll
+    for (int kst = 0; kst < 2; ++kst) {
+      pf[0][kst] = __builtin_bit_cast(f16x8, make_uint4(p0_cur[4 * kst], p0_cur[4 * kst + 1], p0_cur[4 * kst + 2],
+                                                        p0_cur[4 * kst + 3]));
+      pf[1][kst] = __builtin_bit_cast(f16x8, make_uint4(p1[4 * kst], p1[4 * kst + 1], p1[4 * kst + 2],
+                                                        p1[4 * kst + 3]));
+    }
+    // the inline score MFMAs land before the VALU reads them, and their
+    // results and srcC stay live up to here (see attn_prepared_kernel)
+    mfma_wait_tail();
+    asm volatile("" ::"v"(ns[0]), "v"(ns[1]), "v"(bias[0]), "v"(bias[1]));
+    if (__builtin_expect(i + 1 < n_own && tile1 * BN2 + BN2 > N, 0)) {
+      mfma_wait();
+      mask(N - tile1 * BN2, ns[0]);
+      mask(N - tile1 * BN2, ns[1]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- phase B: PV(i) beside block 0 of P(i+1)
+    pa = pb = 0.0f;
+    t01 = t23 = t03 = t45 = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int kst = j >> 2, db = j & 3;
+      o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vr[j], pf[0][kst], o[0][db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      float ea = __builtin_amdgcn_exp2f(ns[0][2 * j]);
+      keep(ea);
+      if (j > 0) {
+        p0_next[j - 1] = pack_f16x2(pa, pb);
+        keep(p0_next[j - 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      o[1][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vr[j], pf[1][kst], o[1][db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      vr[j] = frag(rsrc_v, tile1, j);
+      if (j == 2) { t01 = add_f16x2(p0_next[0], p0_next[1]); keep(t01); }
+      if (j == 4) { t23 = add_f16x2(p0_next[2], p0_next[3]); keep(t23); }
+      if (j == 5) { t03 = add_f16x2(t01, t23); keep(t03); }
+      if (j == 6) { t45 = add_f16x2(p0_next[4], p0_next[5]); keep(t45); }
+      float eb = __builtin_amdgcn_exp2f(ns[0][2 * j + 1]);
+      keep(eb);
+      __builtin_amdgcn_sched_barrier(0);
+      pa = ea;
+      pb = eb;
+    }
+    p0_next[7] = pack_f16x2(pa, pb);
+    l0_next = sum_f16x2(add_f16x2(t03, add_f16x2(t45, add_f16x2(p0_next[6], p0_next[7]))));
+    keep(p0_next[7]);
+    keep(l0_next);
+    tile1 = tile2;
+  };
+
+  // The loop takes two tiles a trip; of an odd count the first tile goes ahead
+  // of it.  (A short walk leaves some waves without keys.)
+  f32x16 sa[2], sb[2];
+  uint32_t pA[8], pB[8];
+  float lA, lB = 0.0f;
+  // the fp16 words of a tile's block and their sum
+  auto words = [&](const f32x16& s, uint32_t* w, float& sum) __attribute__((always_inline)) {
+    float la = 0.0f, lb = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float ea = __builtin_amdgcn_exp2f(s[2 * j]);
+      const float eb = __builtin_amdgcn_exp2f(s[2 * j + 1]);
+      w[j] = pack_f16x2(ea, eb);
+      la += ea;
+      lb += eb;
+    }
+    sum = la + lb;
+  };
+  if (n_own & 1) {
+    const int tile = walk_tile(t0, entry_of(t0));
+    scores(tile, sa[0], sa[1]);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      sa[qb] -= m_ref[qb];
+      words(sa[qb], pA, lA);
+      l_run[qb] = lA;
+      ovf = fmaxf(ovf, lA);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int kst = j >> 2;
+        const f16x8 pf = __builtin_bit_cast(f16x8, make_uint4(pA[4 * kst], pA[4 * kst + 1], pA[4 * kst + 2], pA[4 * kst + 3]));
+        o[qb][j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag(rsrc_v, tile, j), pf, o[qb][j & 3], 0, 0, 0);
+      }
+    }
+    ++t0;
+    --n_own;
+  }
+  const int tile_0 = walk_tile(t0, entry_of(t0));
+  scores(tile_0, sa[0], sa[1]);
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) sa[qb] -= m_ref[qb];
+  words(sa[0], pA, lA);
+  tile1 = walk_tile(t0 + 1, entry_of(t0 + 1));
+  entry2 = entry_of(t0 + 2);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) kr[j] = frag(rsrc_k, tile1, j);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) vr[j] = frag(rsrc_v, tile_0, j);
+  // Q' is in AGPRs from here on, where the inline score MFMAs read it: a copy
+  // into them right before one of those would be a hazard the compiler, which
+  // cannot see the MFMA, does not wait out (a build test checks it).
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+a"(qf[0][kk]), "+a"(qf[1][kk]));
+  mfma_wait();
+  for (int i = 0; i < n_own; i += 2) {
+    iteration(i, sa, sb, pA, pB, lA, lB);
+    iteration(i + 1, sb, sa, pB, pA, lB, lA);
+    if (__builtin_expect(__any(ovf > kP16SumLimit), 0)) break;
+  }
+
+  // ---- the waves' partial sums meet in LDS
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4)
+        red[(((wave * 2 + qb) * 4 + db) * 4 + g4) * 64 + lane] =
+            make_float4(o[qb][db][4 * g4], o[qb][db][4 * g4 + 1], o[qb][db][4 * g4 + 2], o[qb][db][4 * g4 + 3]);
+    red_l[(wave * 2 + qb) * 64 + lane] = l_run[qb];
+  }
+  const bool over = __any(ovf > kP16SumLimit);
+  if (lane == 0) red_mark[wave] = over;
+  __syncthreads();
+  const bool marked = (red_mark[0] | red_mark[1] | red_mark[2] | red_mark[3]) != 0;
+
+  // ---- epilogue: wave w writes dims [32w, 32w + 32): register j is dim 32w + 8(j/4) + 4hh + j%4
+  const int ob = bh / heads;
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int row = qrow0 + 32 * qb;
+    float l_tot = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves2; ++w)
+      l_tot += red_l[(w * 2 + qb) * 64 + lane] + red_l[(w * 2 + qb) * 64 + (lane ^ 32)];
+    const float inv = 1.0f / l_tot;
+    float x[16];
+    float sum = inv;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      float4 a = red[((qb * 4 + wave) * 4 + g4) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kWaves2; ++w) {
+        const float4 b = red[(((w * 2 + qb) * 4 + wave) * 4 + g4) * 64 + lane];
+        a = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+      }
+      const float e[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        x[4 * g4 + c] = e[c] * inv;
+        sum += e[c];
+      }
+    }
+    if (!marked) note_range(f32_nonfinite(sum) && row < Nq, SOL_RANGE_OUT);
+    if (row >= Nq) continue;
+    if (kOutRec) {
+      uint8_t* dst = reinterpret_cast<uint8_t*>(out) + (((size_t)ob * Nq + row) * heads + (bh - ob * heads)) * kOutRecBytes;
+      if (wave == 0 && hh == 0) *reinterpret_cast<uint3*>(dst + 132) = make_uint3(0u, 0u, 0u);
+      if (marked) {
+        if (hh == 0) dst[128 + wave] = 0xFF;
+        continue;
+      }
+      float a = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) a = fmaxf(a, __builtin_fabsf(x[j]));
+      a = fmaxf(a, __shfl_xor(a, 32));
+      const uint32_t sc = ue5m3_scale_for(a);
+      const float sv = ue5m3_value(sc);
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w |= int8_code(x[4 * g4 + e], sv) << (8 * e);
+        *reinterpret_cast<uint32_t*>(dst + 32 * wave + 8 * g4 + 4 * hh) = w;
+      }
+      if (hh == 0) dst[128 + wave] = (uint8_t)sc;
+    } else if (out_format == 1) {
+      uint8_t* dst = reinterpret_cast<uint8_t*>(out) + slab + (size_t)row * D;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w |= f32_to_e4m3(x[4 * g4 + e]) << (8 * e);
+        *reinterpret_cast<uint32_t*>(dst + 32 * wave + 8 * g4 + 4 * hh) = marked ? 0x7F7F7F7Fu : w;
+      }
+    } else {
+      uint16_t* dst = out + slab + (size_t)row * D;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        uint2 w;
+        w.x = pack_bf16x2(x[4 * g4], x[4 * g4 + 1]);
+        w.y = pack_bf16x2(x[4 * g4 + 2], x[4 * g4 + 3]);
+        if (marked) w = make_uint2(0x7FC07FC0u, 0x7FC07FC0u);
+        *reinterpret_cast<uint2*>(dst + 32 * wave + 8 * g4 + 4 * hh) = w;
+      }
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int64_t rows, const SeqGrid& g,
@@ -1605,6 +2029,14 @@ hipError_t launch_prepare_kv_records(const uint8_t* rec, uint16_t* k_prep, uint1
   return hipGetLastError();
 }
 
+// Whether `units` blocks of 64 query rows run with the keys split: when the
+// whole grid takes at most two rounds of the 256 CUs that way.  One such round
+// costs 0.37 of a sweep of whole 256-row tiles, two 0.74, three 1.1, whatever
+// part of a round the last one is (measured: 12,480 keys, 195 units 233 -> 86
+// us; 3,600 keys, 285 units 80 -> 60 us and 570 units 83 -> 90 us; 1,024 keys,
+// 16 units 32 -> 18 us).
+static bool keys_split(int64_t units) { return units <= 2 * 256; }
+
 hipError_t launch_attn_fwd_prepared(const uint16_t* q, const uint16_t* k_prep,
                                     const uint16_t* v_prep, void* out_v, int BH,
                                     const SeqGrid& g, int n_kv, const float2* tab,
@@ -1619,12 +2051,25 @@ hipError_t launch_attn_fwd_prepared(const uint16_t* q, const uint16_t* k_prep,
   const int64_t per_slab =
       sparse ? (int64_t)kXcds * ((sparse_order_len(n_qtiles, sparse_order_stride(g.hw)) + kXcds - 1) / kXcds)
              : n_qtiles;
+  const bool orec = out_format == 2;
+  const int units = (g.n + kSplitRows - 1) / kSplitRows;  // per slab
+  const bool split = (sparse || nkb == 0) && keys_split((int64_t)units * BH);
+  if (split) {
+#define SOL_SPLIT(R, S, Q) (orec ? attn_keysplit_kernel<R, S, Q, true> : attn_keysplit_kernel<R, S, Q, false>)
+    auto* kernel = qrec     ? SOL_SPLIT(false, false, true)
+                   : sparse ? (tab ? SOL_SPLIT(true, true, false) : SOL_SPLIT(false, true, false))
+                            : (tab ? SOL_SPLIT(true, false, false) : SOL_SPLIT(false, false, false));
+#undef SOL_SPLIT
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(units * BH)), dim3(256), 0, stream, q, k_prep, v_prep, out, g, tab,
+                       units, c_log2, n_kv, q_gamma, eps, out_format, blocks, counts, nkb, qrec, heads);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  // First pass (unless that was it), then the second over the row blocks whose
+  // probabilities left the fp16 range.
   const dim3 grid((unsigned)(per_slab * BH));
-  // First pass, then the second over the row blocks whose probabilities left
-  // the fp16 range.
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = split ? 1 : 0; pass < 2; ++pass) {
     // queries from records: no rotation, no normalisation, dense
-    const bool orec = out_format == 2;
     const int sel = (qrec != nullptr ? 8 + pass : (tab != nullptr) * 4 + pass * 2 + sparse) + 10 * orec;
 #define SOL_LAUNCH_PREPARED(R, P, S, Q, O)                                                      \
   hipLaunchKernelGGL((attn_prepared_kernel<R, P, S, Q, O>), grid, dim3(256), 0, stream, q,       \

@@ -1,0 +1,125 @@
+"""The key-split first pass (64 query rows a workgroup, a quarter of the keys a
+wave), taken where a grid has at most 512 such units, against whole 256-row
+tiles: the same slabs in a call just over the line.  The two sum the keys in
+another order (and round each probability to fp16 alike), so bf16 outputs agree
+to the rounding of the output, and nearly all are equal."""
+import pytest
+import torch
+
+from paper_2609_35110_amd import sol
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    sol.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+def _slabs(rows):
+    """The largest number of slabs of that many rows that splits, and one over."""
+    n = 512 // -(-rows // 64)
+    return n, n + 1
+
+
+def _qkv(slabs, rows, keys, seed):
+    gen = torch.Generator(DEV).manual_seed(seed)
+    draw = lambda n: torch.randn((1, slabs, n, 128), generator=gen, device=DEV).bfloat16()
+    return draw(rows), draw(keys), draw(keys)
+
+
+def _check(split, whole, label):
+    """The two start a tile's scores from -m or subtract m after, so a
+    probability may round to the other fp16 neighbour, 2^-11 of itself: the
+    outputs, means of v weighted by probabilities that sum to one, move by at
+    most 2^-11 of a weighted mean of |v| (below 2 for these v); the row sums by
+    2^-11 (fp16 word sums against fp32).  Then each is rounded to bf16: one
+    step, at most 2^-7 of it."""
+    a, b = split.float(), whole.float()
+    bound = torch.maximum(a.abs(), b.abs()) * (2.0 ** -7 + 2.0 ** -11) + 2.0 ** -10
+    assert bool(((a - b).abs() <= bound).all()), (label, float(((a - b).abs() - bound).max()))
+    assert float((a == b).float().mean()) >= 0.9, label
+
+
+# rows around a unit and a tile; keys around a tile, a block of four, and walks
+# that leave waves without keys or with an odd number of tiles
+SHAPES = [(64, 1), (1, 31), (63, 33), (65, 128), (64, 129), (257, 160), (300, 257), (100, 1000), (513, 700)]
+
+
+@pytest.mark.parametrize("rows,keys", SHAPES)
+def test_dense_equals_whole_tiles(rows, keys):
+    n, over = _slabs(rows)
+    q, k, v = _qkv(over, rows, keys, 100 * rows + keys)
+    outs = []
+    for s in (n, over):
+        kp, vp = sol.prepared_kv_buffers(1, s, keys, DEV)
+        sol.prepare_kv_ex(k[:, :s].contiguous(), v[:, :s].contiguous(), 0, 0, 0, None, kp, vp)
+        outs.append(sol.attn_fwd_prepared_ex(q[:, :s].contiguous(), kp, vp, keys, 0, 0, 0))
+    _check(outs[0], outs[1][:, :n], "%dx%d" % (rows, keys))
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "int8_records"])
+def test_coded_outputs_equal_whole_tiles(fmt):
+    """E4M3 codes and output records: codes differ only where a value lies
+    within the two results' difference (~2e-4 of the RMS) of a midpoint; every
+    byte of a record is written (the padding zero)."""
+    rows, keys = 300, 700
+    n, over = _slabs(rows)
+    q, k, v = _qkv(over, rows, keys, 7)
+    outs = []
+    for s in (n, over):
+        kp, vp = sol.prepared_kv_buffers(1, s, keys, DEV)
+        sol.prepare_kv_ex(k[:, :s].contiguous(), v[:, :s].contiguous(), 0, 0, 0, None, kp, vp)
+        shape = (1, s, rows, 128) if fmt == "fp8" else (1, rows, s, 144)
+        out = torch.full(shape, 0x55, dtype=torch.uint8, device=DEV)
+        outs.append(sol.attn_fwd_prepared_ex(q[:, :s].contiguous(), kp, vp, keys, 0, 0, 0, out=out, **{fmt: True}))
+    a, b = outs[0], outs[1][:, :n] if fmt == "fp8" else outs[1][:, :, :n]
+    if fmt == "int8_records":
+        assert int(a[..., 132:].max()) == 0
+        same = (a[..., 128:132] == b[..., 128:132]).all(-1)  # groups on the same scales
+        assert float(same.float().mean()) >= 0.98
+        a, b = a[..., :128].view(torch.int8).int(), b[..., :128].view(torch.int8).int()
+        assert int((a - b).abs()[same].max()) <= 1
+    assert float((a == b).float().mean()) >= 0.98
+
+
+@pytest.mark.parametrize("tau", [-1e30, 0.5, 1e30])
+def test_block_sparse_equals_whole_tiles(tau):
+    """Lists of every length, a prefix across blocks, a ragged last block."""
+    T, Hl, Wl, nt = 3, 11, 13, 300
+    rows = nt + T * Hl * Wl
+    n, over = _slabs(rows)
+    q, k, v = _qkv(over, rows, rows, 11)
+    tab = sol.rope3d_table(T, Hl, Wl, device=DEV)
+    outs = []
+    for s in (n, over):
+        qs = q[:, :s].contiguous()
+        kp, vp = sol.prepare_kv(k[:, :s].contiguous(), v[:, :s].contiguous(), T, Hl, Wl, tab)
+        ws = sol.sparse_route(qs, kp, T, Hl, Wl, tab, tau)
+        outs.append(sol.attn_fwd_sparse(qs, kp, vp, T, Hl, Wl, tab, ws))
+    _check(outs[0], outs[1][:, :n], "sparse %g" % tau)
+
+
+def test_overflowing_rows_go_to_the_second_pass():
+    """Scores that peak 49 binades up in keys 200 to 400 -- neither the first
+    tile nor the rows' diagonal one -- leave the fp16 range in one or two waves
+    of a unit: its rows are recomputed, in every output format."""
+    rows, keys = 130, 900
+    n, over = _slabs(rows)
+    q, k, v = _qkv(over, rows, keys, 13)
+    q = torch.ones_like(q)
+    at = torch.arange(keys, device=DEV)
+    k = (k * 0.05 + 3 * torch.exp(-((at - 300) / 60.0) ** 2)[:, None]).bfloat16()
+    for how in ({}, {"fp8": True}, {"int8_records": True}):
+        outs = []
+        for s in (n, over):
+            kp, vp = sol.prepared_kv_buffers(1, s, keys, DEV)
+            sol.prepare_kv_ex(k[:, :s].contiguous(), v[:, :s].contiguous(), 0, 0, 0, None, kp, vp)
+            outs.append(sol.attn_fwd_prepared_ex(q[:, :s].contiguous(), kp, vp, keys, 0, 0, 0, **how))
+        whole = outs[1][:, :, :n] if "int8_records" in how else outs[1][:, :n]
+        assert torch.equal(outs[0], whole), how  # both are the second pass's

@@ -209,20 +209,13 @@ __device__ __forceinline__ uint4 rope_chunk(uint4 x, const float2* __restrict__ 
 // in a loop that rotates every key once per query tile).  Within one bf16 ulp
 // of rope_rotate_exact; the two differ where the exact result lies within a
 // few 2^-24 |(a, b)| of a rounding midpoint.
+__device__ __forceinline__ uint32_t rope_pair_fast(uint32_t w, float c, float s) {
+  const float a = __uint_as_float(w << 16), b = __uint_as_float(w & 0xffff0000u);
+  return pack_bf16x2(__builtin_fmaf(a, c, -(b * s)), __builtin_fmaf(a, s, b * c));
+}
 __device__ __forceinline__ uint4 rope_rotate_fast(uint4 x, float4 cs01, float4 cs23) {
-  float f[8];
-  unpack_bf16x8(x, f);
-  const float c[4] = {cs01.x, cs01.z, cs23.x, cs23.z};
-  const float s[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
-  uint32_t w[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const float a = f[2 * u], b = f[2 * u + 1];
-    const float ar = __builtin_fmaf(a, c[u], -(b * s[u]));
-    const float br = __builtin_fmaf(a, s[u], b * c[u]);
-    w[u] = pack_bf16x2(ar, br);
-  }
-  return make_uint4(w[0], w[1], w[2], w[3]);
+  return make_uint4(rope_pair_fast(x.x, cs01.x, cs01.y), rope_pair_fast(x.y, cs01.z, cs01.w),
+                    rope_pair_fast(x.z, cs23.x, cs23.y), rope_pair_fast(x.w, cs23.z, cs23.w));
 }
 
 // ------------------------------------------------------- LDS poison (debug)

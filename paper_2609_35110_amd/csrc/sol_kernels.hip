@@ -317,9 +317,6 @@ constexpr int kTabLdsPairs = 6144;  // rotary tables up to 48 KB are staged in L
 constexpr float kP16SumLimit = 32768.0f;
 static_assert(kThreads == 8 * BN, "staging: one tile row per 8 threads, two 16-byte chunks each");
 
-// Scheduling-group masks of __builtin_amdgcn_sched_group_barrier.
-constexpr int kSgMfma = 0x008, kSgValu = 0x002, kSgDsRead = 0x100, kSgDsWrite = 0x200;
-
 // First table pair of chunk c (< 8: frame or row axis) and c + 8 (row or column
 // axis) under the default 32/48/48 split -- the only one sol_attn_fwd, whose
 // signature carries no split, launches this kernel with -- in two selects
@@ -333,12 +330,18 @@ __device__ __forceinline__ int tab_pair_hi(int c, const Pos& p, const SeqGrid& g
 static_assert(kSplitT == 32 && kSplitH == 48 && kSplitW == 48, "tab_pair_lo/hi assume 32/48/48");
 
 // Software pipeline, per wave, one barrier per 64-key tile.  Iteration i:
-//   phase A (one scheduling region): S(i+1) = K^(i+1) Q^^T on the matrix
-//     cores, interleaved with P(i) = exp2(S(i) c - m c) and its row sums on
-//     the VALU -- independent work, so the two pipes overlap;
-//   phase B (one region): O^T += V(i)^T P(i)^T on the matrix cores,
-//     interleaved with staging K(i+2) (rotated, bf16) and V(i+1) (fp16) from
-//     registers into LDS;
+//   phase A: S(i+1) = K^(i+1) Q^^T on the matrix cores, interleaved with P(i) =
+//     exp2(S(i) c - m c) and its row sums on the VALU -- independent work, so
+//     the two pipes overlap;
+//   phase B: O^T += V(i)^T P(i)^T on the matrix cores, interleaved with staging
+//     K(i+2) (rotated, bf16) and V(i+1) (fp16) from registers into LDS;
+// Both are laid out in sixteen slots of one MFMA and about seven (A) or five (B)
+// VALU instructions; a fragment is read from LDS four MFMAs ahead of its own.
+// (Left to scheduling groups each read stood right before its MFMA, and two
+// waves a SIMD cannot hide an LDS latency per MFMA: 12,480 keys x 24 heads took
+// 2.20 ms, 2.02 ms in slots.)  What bounds it now is instruction issue: 261
+// VALU and MFMA instructions and 60 LDS ones a wave and tile, 80 % of the
+// SIMD's cycles for its two waves.
 //   then the mask, row max and (rare) lazy rescale for tile i+1.
 // K runs one tile ahead of V.  LDS: K(i+1) is read while K(i+2) is written
 // over K(i) (last read in iteration i-1); V(i) is read while V(i+1) is
@@ -511,78 +514,97 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
 
   const int n_kv = (N + BN - 1) / BN;
   auto iteration = [&](int it, f32x16& cs0, f32x16& cs1, f32x16& ns0, f32x16& ns1) {
+    // fragment idx of the tile's sixteen K fragments (two 32-key blocks) and of
+    // its sixteen V fragments, in the order of their MFMAs
+    const uint16_t* kb = k_lds[(it + 1) & 1];
+    const uint16_t* vb = v_lds[it & 1] + v_off;
+    auto kf_at = [&](int idx) __attribute__((always_inline)) { return kfrag(kb, idx & 1, idx >> 1); };
+    auto vf_at = [&](int idx) __attribute__((always_inline)) {
+      const uint16_t* p0 = vb + 16 * (idx >> 2) * VS + 32 * (idx & 3);
+      const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p0);
+      const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 8 * VS));
+      return __builtin_bit_cast(f16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
     load_kv((it + 2) * BN, (it + 1) * BN);
-    fetch_k_rotation((it + 2) * BN);
+    bf16x8 kf[4];
+    f16x8 vf[4];
+#pragma unroll
+    for (int idx = 0; idx < 4; ++idx) kf[idx] = kf_at(idx);
     __builtin_amdgcn_sched_barrier(0);  // issue the loads first: phase B consumes them
+    fetch_k_rotation((it + 2) * BN);
+    __builtin_amdgcn_sched_barrier(0);
     // ---- phase A: S(it+1) on MFMA; P(it) and its row sums on VALU.
-    {
-      const uint16_t* kb = k_lds[(it + 1) & 1];
-      ns0 = f32x16{};
-      ns1 = f32x16{};
-      const float mc = m_run * c_log2;
-      // P in fp16 pairs: word w holds logits 2w and 2w+1 (s0[0..15] then s1[0..15])
-      uint32_t pw[16];
-      float la = 0.0f, lb = 0.0f;
+    const float mc = m_run * c_log2;
+    // P in fp16 pairs: word w holds logits 2w and 2w+1 (s0[0..15] then s1[0..15])
+    uint32_t pw[16];
+    float la = 0.0f, lb = 0.0f, pa = 0.0f, pb = 0.0f;
+    ns0 = f32x16{};
+    ns1 = f32x16{};
+    // a pair's word and row sums (fp32 adds: v_dot2_f32_f16 would share the
+    // matrix pipe with the MFMAs and cost about half an MFMA each)
+    auto finish = [&](int w) __attribute__((always_inline)) {
+      f16x2 h;
+      h[0] = (_Float16)pa;
+      h[1] = (_Float16)pb;
+      pw[w] = __builtin_bit_cast(uint32_t, h);
+      asm volatile("" : "+v"(pw[w]));
+      const f16x2 one = {(_Float16)1.0f, (_Float16)1.0f};
+      if (w & 1) la = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw[w]), one, la, false);
+      else lb = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw[w]), one, lb, false);
+    };
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        ns0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(kb, 0, kk), qf[kk], ns0, 0, 0, 0);
-        ns1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(kb, 1, kk), qf[kk], ns1, 0, 0, 0);
-        // logits 4kk .. 4kk+3 of this lane
+    for (int idx = 0; idx < 16; ++idx) {
+      f32x16& ns = (idx & 1) ? ns1 : ns0;
+      ns = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[idx & 3], qf[idx >> 1], ns, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (idx + 4 < 16) kf[idx & 3] = kf_at(idx + 4);
+      else vf[idx & 3] = vf_at(idx - 12);
+      if (idx > 0) finish(idx - 1);
+      const float a = idx < 8 ? cs0[2 * idx] : cs1[2 * idx - 16];
+      const float b = idx < 8 ? cs0[2 * idx + 1] : cs1[2 * idx - 15];
+      pa = __builtin_amdgcn_exp2f(__builtin_fmaf(a, c_log2, -mc));
+      pb = __builtin_amdgcn_exp2f(__builtin_fmaf(b, c_log2, -mc));
+      asm volatile("" : "+v"(pa), "+v"(pb));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    finish(15);
+    if (__any(la + lb > kP16SumLimit)) {  // rare: m lags this tile by > 2^15
+      fold_max(cs0, cs1);
+      probs(cs0, cs1, pw, la, lb);
+    }
+    l_run += la + lb;
+    f16x8 pf[4];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int idx = 4 * kk + 2 * u;
-          const float a = idx < 16 ? cs0[idx] : cs1[idx - 16];
-          const float b = idx < 16 ? cs0[idx + 1] : cs1[idx - 15];
-          const float ea = __builtin_amdgcn_exp2f(__builtin_fmaf(a, c_log2, -mc));
-          const float eb = __builtin_amdgcn_exp2f(__builtin_fmaf(b, c_log2, -mc));
-          f16x2 h;
-          h[0] = (_Float16)ea;
-          h[1] = (_Float16)eb;
-          pw[2 * kk + u] = __builtin_bit_cast(uint32_t, h);
-          // row sums in fp32 adds: v_dot2_f32_f16 would share the matrix
-          // pipe with the MFMAs and cost about half an MFMA each
-          la += ea;
-          lb += eb;
+    for (int t = 0; t < 4; ++t)
+      pf[t] = __builtin_bit_cast(f16x8, make_uint4(pw[4 * t], pw[4 * t + 1], pw[4 * t + 2], pw[4 * t + 3]));
+    // ---- phase B: O^T += V(it)^T P(it)^T on MFMA; on VALU the staging of
+    // K(it+2) (a rotary pair in the even slots) and V(it+1) (a word in the odd
+    // ones), a chunk's write as soon as it is whole.
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t kw[4], vw[4];
+#pragma unroll
+    for (int idx = 0; idx < 16; ++idx) {
+      o[idx & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[idx & 3], pf[idx >> 2], o[idx & 3], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (idx + 4 < 16) vf[idx & 3] = vf_at(idx + 4);
+      const int u = idx >> 3, j = (idx >> 1) & 3;  // the thread's chunk and its pair
+      auto word = [&](const uint4& x) __attribute__((always_inline)) { return j == 0 ? x.x : j == 1 ? x.y : j == 2 ? x.z : x.w; };
+      if ((idx & 1) == 0) {
+        kw[j] = word(kreg[u]);
+        if (kRope) {
+          const float4 t = kcs[2 * u + (j >> 1)];
+          kw[j] = rope_pair_fast(kw[j], (j & 1) ? t.z : t.x, (j & 1) ? t.w : t.y);
         }
+        asm volatile("" : "+v"(kw[j]));
+      } else {
+        vw[j] = bf16x2_to_f16x2(word(vreg[u]));
+        asm volatile("" : "+v"(vw[j]));
       }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(kSgMfma, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(kSgValu, 12, 0);
+      if ((idx & 7) == 7) {
+        *reinterpret_cast<uint4*>(&k_lds[it & 1][rr * KS + c0 * 8 + 64 * u]) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
+        *reinterpret_cast<uint4*>(&v_lds[(it + 1) & 1][rr * VS + c0 * 8 + 64 * u]) = make_uint4(vw[0], vw[1], vw[2], vw[3]);
       }
-      if (__any(la + lb > kP16SumLimit)) {  // rare: m lags this tile by > 2^15
-        fold_max(cs0, cs1);
-        probs(cs0, cs1, pw, la, lb);
-      }
-      l_run += la + lb;
-      f16x8 pb[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        pb[t] = __builtin_bit_cast(f16x8, make_uint4(pw[4 * t], pw[4 * t + 1], pw[4 * t + 2], pw[4 * t + 3]));
-      // ---- phase B: O^T += V(it)^T P(it)^T on MFMA; staging on VALU.
-      const uint16_t* vb = v_lds[it & 1] + v_off;
-#pragma unroll
-      for (int kst = 0; kst < 4; ++kst) {
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-          const uint16_t* p0 = vb + 16 * kst * VS + 32 * db;
-          const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p0);
-          const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 8 * VS));
-          const f16x8 a = __builtin_bit_cast(
-              f16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pb[kst], o[db], 0, 0, 0);
-        }
-      }
-      store_k(it & 1);
-      store_v((it + 1) & 1);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2, 1);
-        __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 1);
-        __builtin_amdgcn_sched_group_barrier(kSgValu, 6, 1);
-      }
-      __builtin_amdgcn_sched_group_barrier(kSgDsWrite, 4, 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     if (it + 1 < n_kv && (it + 2) * BN > N) mask_tile(it + 1, ns0, ns1);
     __syncthreads();

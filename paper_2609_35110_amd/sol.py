@@ -9,6 +9,7 @@ step of the computation runs in the HIP library; there is no fallback: if
 libsol.so is missing or fails to load, every call raises.
 """
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -287,10 +288,21 @@ def rope3d_table(T, Hl, Wl, D=HEAD_DIM, base=ROPE_BASE, device="cuda", split=Non
 
 
 def _stream(t):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """The current HIP stream of t's device (the raw handle, without the Stream
+    object that torch.cuda.current_stream builds round it)."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
+
+# A small call is bound by this module, not by its kernels (a rotation of 64 rows
+# took 7.7 us of host time against 3 us on the GPU), so what every call does is
+# kept short: the checks accept a good tensor in one expression and look for the
+# fault only in one that is not; pointers and streams go to ctypes as integers;
+# the table size a grid and split need is looked up.
 
 def _check_tensor(name, t, shape=None):
+    if (isinstance(t, torch.Tensor) and t.dtype is torch.bfloat16 and t.is_cuda and t.dim() == 4
+            and t.is_contiguous() and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != torch.bfloat16:
@@ -303,6 +315,11 @@ def _check_tensor(name, t, shape=None):
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
 
 
+@functools.lru_cache(maxsize=256)
+def _table_floats(D, T, Hl, Wl, split):
+    return sol_rope3d_table_floats_ex(D, T, Hl, Wl, *split)
+
+
 def _table_ptr(table, dev, D, T, Hl, Wl, split=None):
     """The device pointer of a rotary table, checked against the size the
     grid and split give it (the C ABI takes a bare pointer and finds the
@@ -312,11 +329,11 @@ def _table_ptr(table, dev, D, T, Hl, Wl, split=None):
         return None
     if table.dtype != torch.float32 or table.device != dev or not table.is_contiguous():
         raise ValueError("rope table must be a contiguous float32 tensor on %s" % dev)
-    need = sol_rope3d_table_floats_ex(D, T, Hl, Wl, *_split(split))
+    need = _table_floats(D, T, Hl, Wl, _split(split))
     if T * Hl * Wl > 0 and table.numel() != need:
         raise ValueError("rope table holds %d floats; grid %dx%dx%d and split %s need %d"
                          % (table.numel(), T, Hl, Wl, _split(split), need))
-    return ctypes.c_void_p(table.data_ptr())
+    return table.data_ptr()
 
 
 def rope3d(x, T, Hl, Wl, table, out=None):
@@ -326,7 +343,7 @@ def rope3d(x, T, Hl, Wl, table, out=None):
     if out is None:
         out = torch.empty_like(x)
     _check_tensor("out", out, x.shape)
-    check(sol_rope3d(ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H, N, D,
+    check(sol_rope3d(x.data_ptr(), out.data_ptr(), B, H, N, D,
                      T, Hl, Wl, _table_ptr(table, x.device, D, T, Hl, Wl, None), _stream(x)))
     return out
 
@@ -338,7 +355,7 @@ def _gamma_ptr(gamma, dev):
             or not gamma.is_contiguous() or gamma.shape != (HEAD_DIM,)):
         raise ValueError("gamma must be a contiguous float32 tensor of %d weights on %s"
                          % (HEAD_DIM, dev))
-    return ctypes.c_void_p(gamma.data_ptr())
+    return gamma.data_ptr()
 
 
 def qknorm_rope3d(x, T, Hl, Wl, table, gamma, eps=1e-6, out=None, split=None):
@@ -348,7 +365,7 @@ def qknorm_rope3d(x, T, Hl, Wl, table, gamma, eps=1e-6, out=None, split=None):
     if out is None:
         out = torch.empty_like(x)
     _check_tensor("out", out, x.shape)
-    check(sol_qknorm_rope3d(ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H,
+    check(sol_qknorm_rope3d(x.data_ptr(), out.data_ptr(), B, H,
                             N, D, T, Hl, Wl, *_split(split), _table_ptr(table, x.device, D, T, Hl, Wl, split),
                             _gamma_ptr(gamma, x.device), float(eps), _stream(x)))
     return out
@@ -363,8 +380,8 @@ def attn_fwd(q, k, v, T, Hl, Wl, table=None, out=None):
     if out is None:
         out = torch.empty_like(q)
     _check_tensor("out", out, q.shape)
-    check(sol_attn_fwd(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()),
-                       ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H, N, D,
+    check(sol_attn_fwd(q.data_ptr(), k.data_ptr(),
+                       v.data_ptr(), out.data_ptr(), B, H, N, D,
                        T, Hl, Wl, _table_ptr(table, q.device, D, T, Hl, Wl, None), _stream(q)))
     return out
 
@@ -390,10 +407,10 @@ def attn_fwd_ws(q, k, v, T, Hl, Wl, table=None, workspace=None, out=None):
     if not workspace.is_cuda or workspace.device != q.device or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous tensor on %s" % q.device)
     nbytes = workspace.numel() * workspace.element_size()
-    check(sol_attn_fwd_ws(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()),
-                          ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H, N,
+    check(sol_attn_fwd_ws(q.data_ptr(), k.data_ptr(),
+                          v.data_ptr(), out.data_ptr(), B, H, N,
                           D, T, Hl, Wl, _table_ptr(table, q.device, D, T, Hl, Wl, None),
-                          ctypes.c_void_p(workspace.data_ptr()), nbytes, _stream(q)))
+                          workspace.data_ptr(), nbytes, _stream(q)))
     return out
 
 
@@ -407,8 +424,8 @@ def attn_fwd_noalloc(q, k, v, T, Hl, Wl, table=None, out=None):
     if out is None:
         out = torch.empty_like(q)
     _check_tensor("out", out, q.shape)
-    check(sol_attn_fwd_noalloc(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()),
-                               ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H, N,
+    check(sol_attn_fwd_noalloc(q.data_ptr(), k.data_ptr(),
+                               v.data_ptr(), out.data_ptr(), B, H, N,
                                D, T, Hl, Wl, _table_ptr(table, q.device, D, T, Hl, Wl, None), _stream(q)))
     return out
 
@@ -435,8 +452,8 @@ def prepare_kv(k, v, T, Hl, Wl, table=None, k_prep=None, v_prep=None):
         v_prep = torch.empty(nbytes // 2, dtype=torch.float16, device=k.device)
     _check_prepared("k_prep", k_prep, nbytes, k.device)
     _check_prepared("v_prep", v_prep, nbytes, k.device)
-    check(sol_prepare_kv(ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),
-                         ctypes.c_void_p(k_prep.data_ptr()), ctypes.c_void_p(v_prep.data_ptr()),
+    check(sol_prepare_kv(k.data_ptr(), v.data_ptr(),
+                         k_prep.data_ptr(), v_prep.data_ptr(),
                          B, H, N, D, T, Hl, Wl, _table_ptr(table, k.device, D, T, Hl, Wl, None), _stream(k)))
     return k_prep, v_prep
 
@@ -451,8 +468,8 @@ def attn_fwd_prepared(q, k_prep, v_prep, T, Hl, Wl, table=None, out=None):
     if out is None:
         out = torch.empty_like(q)
     _check_tensor("out", out, q.shape)
-    check(sol_attn_fwd_prepared(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()),
-                                ctypes.c_void_p(v_prep.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+    check(sol_attn_fwd_prepared(q.data_ptr(), k_prep.data_ptr(),
+                                v_prep.data_ptr(), out.data_ptr(),
                                 B, H, N, D, T, Hl, Wl, _table_ptr(table, q.device, D, T, Hl, Wl, None), _stream(q)))
     return out
 
@@ -476,8 +493,8 @@ def prepare_kv_ex(k, v, T, Hl, Wl, table, k_prep, v_prep, key0=0, n_kv=None, gam
     nbytes = sol_prepared_kv_bytes(B, H, n_kv, D)
     _check_prepared("k_prep", k_prep, nbytes, k.device)
     _check_prepared("v_prep", v_prep, nbytes, k.device)
-    check(sol_prepare_kv_ex(ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),
-                            ctypes.c_void_p(k_prep.data_ptr()), ctypes.c_void_p(v_prep.data_ptr()),
+    check(sol_prepare_kv_ex(k.data_ptr(), v.data_ptr(),
+                            k_prep.data_ptr(), v_prep.data_ptr(),
                             B, H, N, key0, n_kv, D, T, Hl, Wl, *_split(split), _table_ptr(table, k.device, D, T, Hl, Wl, split),
                             _gamma_ptr(gamma, k.device), float(eps), _stream(k)))
     return k_prep, v_prep
@@ -514,8 +531,8 @@ def attn_fwd_prepared_ex(q, k_prep, v_prep, n_kv, T, Hl, Wl, table=None, gamma=N
     _check_prepared("k_prep", k_prep, nbytes, q.device)
     _check_prepared("v_prep", v_prep, nbytes, q.device)
     out, fmt = _out_tensor(out, B, H, N, q.device, fp8, int8_records)
-    check(sol_attn_fwd_prepared_ex(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()),
-                                   ctypes.c_void_p(v_prep.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+    check(sol_attn_fwd_prepared_ex(q.data_ptr(), k_prep.data_ptr(),
+                                   v_prep.data_ptr(), out.data_ptr(),
                                    B, H, N, n_kv, D, T, Hl, Wl, *_split(split), _table_ptr(table, q.device, D, T, Hl, Wl, split),
                                    _gamma_ptr(gamma, q.device), float(eps), fmt, _stream(q)))
     return out
@@ -554,9 +571,9 @@ def sparse_route(q, k_prep, T, Hl, Wl, table, tau, workspace=None, gamma=None, e
         workspace = sparse_workspace(q)
     nbytes = sol_sparse_workspace_bytes(B, H, N, D)
     _check_workspace(workspace, nbytes, q.device)
-    check(sol_sparse_route(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()), B, H,
+    check(sol_sparse_route(q.data_ptr(), k_prep.data_ptr(), B, H,
                            N, D, T, Hl, Wl, *_split(split), _table_ptr(table, q.device, D, T, Hl, Wl, split), _gamma_ptr(gamma, q.device),
-                           float(eps), float(tau), ctypes.c_void_p(workspace.data_ptr()),
+                           float(eps), float(tau), workspace.data_ptr(),
                            workspace.numel() * workspace.element_size(), _stream(q)))
     return workspace
 
@@ -584,11 +601,11 @@ def attn_fwd_sparse(q, k_prep, v_prep, T, Hl, Wl, table, workspace, gamma=None, 
     _check_prepared("v_prep", v_prep, nbytes, q.device)
     _check_workspace(workspace, sol_sparse_workspace_bytes(B, H, N, D), q.device)
     out, fmt = _out_tensor(out, B, H, N, q.device, fp8, int8_records)
-    check(sol_attn_fwd_sparse(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()),
-                              ctypes.c_void_p(v_prep.data_ptr()), ctypes.c_void_p(out.data_ptr()), B, H,
+    check(sol_attn_fwd_sparse(q.data_ptr(), k_prep.data_ptr(),
+                              v_prep.data_ptr(), out.data_ptr(), B, H,
                               N, D, T, Hl, Wl, *_split(split), _table_ptr(table, q.device, D, T, Hl, Wl, split),
                               _gamma_ptr(gamma, q.device),
-                              float(eps), ctypes.c_void_p(workspace.data_ptr()),
+                              float(eps), workspace.data_ptr(),
                               workspace.numel() * workspace.element_size(), fmt, _stream(q)))
     return out
 
@@ -618,8 +635,8 @@ def qkv_encode(q, k, v, T=0, Hl=0, Wl=0, table=None, q_gamma=None, k_gamma=None,
     if rec is None:
         rec = torch.empty((B, N, H, QKV_RECORD_BYTES), dtype=torch.uint8, device=q.device)
     _check_records(rec, B, H, N, q.device)
-    check(sol_qkv_encode(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()),
-                         ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(rec.data_ptr()), B, H, N, D,
+    check(sol_qkv_encode(q.data_ptr(), k.data_ptr(),
+                         v.data_ptr(), rec.data_ptr(), B, H, N, D,
                          T, Hl, Wl, _table_ptr(table, q.device, D, T, Hl, Wl, None), _gamma_ptr(q_gamma, q.device),
                          _gamma_ptr(k_gamma, q.device), float(eps), _stream(q)))
     return rec
@@ -639,7 +656,7 @@ def qkv_encode_packed(qkv, T=0, Hl=0, Wl=0, table=None, q_gamma=None, k_gamma=No
     base, el = qkv.data_ptr(), qkv.element_size()
     check(sol_qkv_encode_strided(ctypes.c_void_p(base), ctypes.c_void_p(base + H * D * el),
                                  ctypes.c_void_p(base + 2 * H * D * el), N * 3 * H * D, D, 3 * H * D,
-                                 ctypes.c_void_p(rec.data_ptr()), B, H, N, D, T, Hl, Wl,
+                                 rec.data_ptr(), B, H, N, D, T, Hl, Wl,
                                  _table_ptr(table, qkv.device, D, T, Hl, Wl, None), _gamma_ptr(q_gamma, qkv.device),
                                  _gamma_ptr(k_gamma, qkv.device), float(eps), _stream(qkv)))
     return rec
@@ -651,8 +668,8 @@ def qkv_decode(rec):
     _check_records(rec, B, H, N, rec.device)
     q, k, v = (torch.empty((B, H, N, HEAD_DIM), dtype=torch.bfloat16, device=rec.device)
                for _ in range(3))
-    check(sol_qkv_decode(ctypes.c_void_p(rec.data_ptr()), ctypes.c_void_p(q.data_ptr()),
-                         ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()), B, H, N,
+    check(sol_qkv_decode(rec.data_ptr(), q.data_ptr(),
+                         k.data_ptr(), v.data_ptr(), B, H, N,
                          HEAD_DIM, _stream(rec)))
     return q, k, v
 
@@ -666,8 +683,8 @@ def prepare_kv_records(rec, k_prep, v_prep, key0=0, n_kv=None):
     nbytes = sol_prepared_kv_bytes(B, H, n_kv, HEAD_DIM)
     _check_prepared("k_prep", k_prep, nbytes, rec.device)
     _check_prepared("v_prep", v_prep, nbytes, rec.device)
-    check(sol_prepare_kv_records(ctypes.c_void_p(rec.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()),
-                                 ctypes.c_void_p(v_prep.data_ptr()), B, H, N, key0, n_kv, HEAD_DIM,
+    check(sol_prepare_kv_records(rec.data_ptr(), k_prep.data_ptr(),
+                                 v_prep.data_ptr(), B, H, N, key0, n_kv, HEAD_DIM,
                                  _stream(rec)))
     return k_prep, v_prep
 
@@ -683,8 +700,8 @@ def attn_fwd_records(rec, k_prep, v_prep, n_kv=None, out=None, fp8=False, int8_r
     _check_prepared("k_prep", k_prep, nbytes, rec.device)
     _check_prepared("v_prep", v_prep, nbytes, rec.device)
     out, fmt = _out_tensor(out, B, H, N, rec.device, fp8, int8_records)
-    check(sol_attn_fwd_records(ctypes.c_void_p(rec.data_ptr()), ctypes.c_void_p(k_prep.data_ptr()),
-                               ctypes.c_void_p(v_prep.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+    check(sol_attn_fwd_records(rec.data_ptr(), k_prep.data_ptr(),
+                               v_prep.data_ptr(), out.data_ptr(),
                                B, H, N, n_kv, HEAD_DIM, fmt, _stream(rec)))
     return out
 
@@ -704,7 +721,7 @@ def mfma_probe(operands, workgroups, iters, out=None):
         raise ValueError("operands must be a contiguous float16 device tensor of 8192 values")
     if out is None:
         out = torch.empty(workgroups * 256, dtype=torch.float32, device=operands.device)
-    check(sol_mfma_probe(ctypes.c_void_p(operands.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+    check(sol_mfma_probe(operands.data_ptr(), out.data_ptr(),
                          workgroups, iters, _stream(operands)))
     return out
 

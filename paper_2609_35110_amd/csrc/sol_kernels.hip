@@ -339,8 +339,8 @@ static_assert(kSplitT == 32 && kSplitH == 48 && kSplitW == 48, "tab_pair_lo/hi a
 // VALU instructions; a fragment is read from LDS four MFMAs ahead of its own.
 // (Left to scheduling groups each read stood right before its MFMA, and two
 // waves a SIMD cannot hide an LDS latency per MFMA: 12,480 keys x 24 heads took
-// 2.20 ms, 2.02 ms in slots.)  What bounds it now is instruction issue: 261
-// VALU and MFMA instructions and 60 LDS ones a wave and tile, 80 % of the
+// 2.20 ms, 2.02 ms in slots.)  What bounds it now is instruction issue: 256
+// VALU and MFMA instructions and 56 LDS ones a wave and tile, 78 % of the
 // SIMD's cycles for its two waves.
 //   then the mask, row max and (rare) lazy rescale for tile i+1.
 // K runs one tile ahead of V.  LDS: K(i+1) is read while K(i+2) is written

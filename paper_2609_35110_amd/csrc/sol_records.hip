@@ -178,6 +178,10 @@ __global__ __launch_bounds__(kEncThreads) void qkv_encode_kernel(
   }
 }
 
+// One thread per 16-byte chunk written, four records a workgroup.  Runs at a
+// copy's rate as it is: 14,400 tokens of 40 heads in 124 us, 5.4 TB/s (the
+// encoder's walk over a token's heads took 134 us: little to share here, and
+// fewer independent loads in flight).
 __global__ __launch_bounds__(kRecThreads) void qkv_decode_kernel(
     const uint8_t* __restrict__ rec, uint4* __restrict__ q, uint4* __restrict__ k,
     uint4* __restrict__ v, int64_t n_rec, int H, int N) {

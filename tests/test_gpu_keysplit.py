@@ -1,5 +1,5 @@
 """The key-split first pass (64 query rows a workgroup, a quarter of the keys a
-wave), taken where a grid has at most 512 such units, against whole 256-row
+wave), taken where a grid has at most 256 such units, against whole 256-row
 tiles: the same slabs in a call just over the line.  The two sum the keys in
 another order (and round each probability to fp16 alike), so bf16 outputs agree
 to the rounding of the output, and nearly all are equal."""
@@ -23,7 +23,7 @@ def _gpu():
 
 def _slabs(rows):
     """The largest number of slabs of that many rows that splits, and one over."""
-    n = 512 // -(-rows // 64)
+    n = 256 // -(-rows // 64)
     return n, n + 1
 
 

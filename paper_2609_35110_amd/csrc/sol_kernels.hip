@@ -339,8 +339,8 @@ static_assert(kSplitT == 32 && kSplitH == 48 && kSplitW == 48, "tab_pair_lo/hi a
 // VALU instructions; a fragment is read from LDS four MFMAs ahead of its own.
 // (Left to scheduling groups each read stood right before its MFMA, and two
 // waves a SIMD cannot hide an LDS latency per MFMA: 12,480 keys x 24 heads took
-// 2.20 ms, 2.02 ms in slots.)  What bounds it now is instruction issue: 256
-// VALU and MFMA instructions and 56 LDS ones a wave and tile, 78 % of the
+// 2.18 ms, 1.92 ms in slots.)  What bounds it now is instruction issue: 270
+// VALU and MFMA instructions and 56 LDS ones a wave and tile, 83 % of the
 // SIMD's cycles for its two waves.
 //   then the mask, row max and (rare) lazy rescale for tile i+1.
 // K runs one tile ahead of V.  LDS: K(i+1) is read while K(i+2) is written
@@ -540,17 +540,17 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     float la = 0.0f, lb = 0.0f, pa = 0.0f, pb = 0.0f;
     ns0 = f32x16{};
     ns1 = f32x16{};
-    // a pair's word and row sums (fp32 adds: v_dot2_f32_f16 would share the
-    // matrix pipe with the MFMAs and cost about half an MFMA each)
+    // a pair's word and row sums: fp32 adds of the unrounded exponentials
+    // (v_dot2_f32_f16 of the words is one instruction less a word, but shares
+    // the matrix pipe: 12,480 keys x 24 heads 1.934 against 1.922 ms)
     auto finish = [&](int w) __attribute__((always_inline)) {
       f16x2 h;
       h[0] = (_Float16)pa;
       h[1] = (_Float16)pb;
       pw[w] = __builtin_bit_cast(uint32_t, h);
       asm volatile("" : "+v"(pw[w]));
-      const f16x2 one = {(_Float16)1.0f, (_Float16)1.0f};
-      if (w & 1) la = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw[w]), one, la, false);
-      else lb = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw[w]), one, lb, false);
+      la += pa;
+      lb += pb;
     };
 #pragma unroll
     for (int idx = 0; idx < 16; ++idx) {

@@ -13,6 +13,7 @@ compiler actually produced:
   * no VALU instruction writes an SGPR that a tile copy reads within the 5
     wait states such a read needs;
   * M0, which the copies set without saving it, is used by nothing else.
+One check concerns the fused kernel: its row sums stay in fp32.
 """
 import os
 import re
@@ -267,3 +268,19 @@ def test_loaded_registers_read_after_their_vmcnt_wait(asm_text):
             if op.startswith(("buffer_", "global_", "scratch_", "flat_")):
                 loads = "load" in op and not t.endswith(" lds")
                 pending.append((i, _vregs(ops[0]) if loads else set()))
+
+
+N_FUSED = 3  # attn_fwd_kernel: no rotation, rotation with the table in LDS or not
+
+
+def test_fused_row_sums_are_fp32_adds(asm_text):
+    """The fused kernel sums a row's fp32 exponentials before they are rounded
+    to fp16 (both the loop and its rare path), never the fp16 words: no dot
+    product instruction, and an fp32 add for each of a loop trip's two tiles'
+    32 exponentials a lane."""
+    kernels = functions(asm_text, "attn_fwd_kernel")
+    assert len(kernels) == N_FUSED
+    for name, body in kernels:
+        ops = [t.split()[0] for t, _ in instructions(body)]
+        assert not any("dot2" in o for o in ops), name
+        assert sum(o.startswith("v_add_f32") for o in ops) >= 64, name

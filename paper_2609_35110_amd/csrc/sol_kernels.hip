@@ -365,6 +365,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int hh = lane >> 5;   // which half of the key block this lane holds
   const int l32 = lane & 31;  // query column of this lane in the score block
   const int bh = blockIdx.x / n_qtiles;
@@ -633,6 +634,12 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   if (it < n_kv) iteration(it, sa0, sa1, sb0, sb1);
 
   // ---- epilogue: out = O / l in bf16; register j of block db is dim 32db + 8(j/4) + 4hh + j%4.
+  // The lane's row and half are found again here, from the lane count and the
+  // wave number in a scalar register: kept across the loop, which takes every
+  // vector register, they would spill.
+  const int e_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int e_row = qt * BM + wave_s * 32 + (e_lane & 31);
+  const int e_hh = e_lane >> 5;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const float inv = 1.0f / l_tot;
   {
@@ -644,10 +651,10 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int j = 0; j < 16; ++j) sum += o[db][j];
-    note_range(f32_nonfinite(sum) && qrow < N, SOL_RANGE_OUT);
+    note_range(f32_nonfinite(sum) && e_row < N, SOL_RANGE_OUT);
   }
-  if (qrow < N) {
-    uint16_t* dst = out + slab + (size_t)qrow * D;
+  if (e_row < N) {
+    uint16_t* dst = out + slab + (size_t)e_row * D;
 #pragma unroll
     for (int db = 0; db < 4; ++db) {
 #pragma unroll
@@ -655,7 +662,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         uint2 w;
         w.x = pack_bf16x2(o[db][4 * g4] * inv, o[db][4 * g4 + 1] * inv);
         w.y = pack_bf16x2(o[db][4 * g4 + 2] * inv, o[db][4 * g4 + 3] * inv);
-        *reinterpret_cast<uint2*>(dst + 32 * db + 8 * g4 + 4 * hh) = w;
+        *reinterpret_cast<uint2*>(dst + 32 * db + 8 * g4 + 4 * e_hh) = w;
       }
     }
   }

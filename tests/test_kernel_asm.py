@@ -13,7 +13,8 @@ compiler actually produced:
   * no VALU instruction writes an SGPR that a tile copy reads within the 5
     wait states such a read needs;
   * M0, which the copies set without saving it, is used by nothing else.
-One check concerns the fused kernel: its row sums stay in fp32.
+Two checks concern the fused kernel: its row sums stay in fp32, and it does
+not spill either.
 """
 import os
 import re
@@ -151,6 +152,10 @@ def test_no_instance_spills(asm_text):
     row blocks); the register budget is checked here instead of trusted."""
     kernels = functions(asm_text, "attn_prepared_kernel")
     assert len(kernels) == N_INSTANCES
+    check_no_spills(kernels)
+
+
+def check_no_spills(kernels):
     for name, body in kernels:
         ins = instructions(body)
         assert not any(t.startswith("scratch_") for t, _ in ins), "%s spills" % name
@@ -284,3 +289,10 @@ def test_fused_row_sums_are_fp32_adds(asm_text):
         ops = [t.split()[0] for t, _ in instructions(body)]
         assert not any("dot2" in o for o in ops), name
         assert sum(o.startswith("v_add_f32") for o in ops) >= 64, name
+
+
+def test_fused_kernel_does_not_spill(asm_text):
+    """Two waves a SIMD leave 256 registers, which the loop takes whole."""
+    kernels = functions(asm_text, "attn_fwd_kernel")
+    assert len(kernels) == N_FUSED
+    check_no_spills(kernels)

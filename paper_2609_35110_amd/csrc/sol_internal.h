@@ -131,6 +131,38 @@ inline int slabs_per_workgroup(int64_t tiles, int64_t bh_count, int64_t want) {
   return (int)(n < 1 ? 1 : n > 8 ? 8 : n);
 }
 
+// Whether the first pass of a prepared call takes `units` workgroups of
+// kSplitRows query rows with the keys split over their waves, in place of whole
+// 256-row tiles.  A round of such units on the 256 CUs costs 0.37 of a sweep of
+// whole tiles, two 0.74, three 1.1, whatever part of a round the last one is
+// (measured, prepared attention: 12,480 keys, 195 units 233 -> 86 us; 3,600
+// keys, 285 units 80 -> 60 us and 570 units 83 -> 90 us; 1,024 keys, 16 units
+// 32 -> 18 us).  So one round always splits, block-sparse walks of any list
+// included (the shortest, one block of 128 keys: 256 units 23.5 -> 19.5 us).
+//
+// A second round pays another 9 us or so of prologue and epilogue, so it needs a
+// long walk.  Over every key (dense; prepare and attention: 192 keys, 255 units
+// 28.9 -> 26.5 us, 384 keys, 240 units 33.4 -> 26.8 us, but 480 units of 384
+// keys 36.4 -> 46.1 us, of 1,024 48.1 -> 52.6 us, of 1,536 57.0 -> 58.0 us, of
+// 2,048 66.3 -> 63.8 us, of 3,072 84.5 -> 78.3 us): from kSplitKeys2 on.  The
+// same for a block-sparse walk with prefix rows, whose query blocks walk every
+// key (384 units of 2,048 keys, the other blocks keeping one: 64 -> 43 us).
+//
+// all_listed: a block-sparse walk without prefix rows, whose units walk their
+// lists alone, an eighth of the keys or so.  Prepare, routing and attention,
+// local inputs, tau 1.0 and 1.5: 4,096 x 8 slabs 90 -> 91 and 83 -> 88 us, 2,048
+// x 16 81 -> 88 and 78 -> 86 us, 10,240 x 3 116 -> 111 and 93 -> 96 us, 10,752 x
+// 2 95 -> 89 us (tau 1.5), 16,384 x 2 136 -> 120 and 106 -> 98 us, 31,744 x 1
+// 186 -> 154 and 131 -> 115 us: from kSplitKeys2Listed on, where these gain at
+// every tau of 1.0 to 1.5.  (Lists far shorter than those lose there, by those 9
+// us: the attention of 16,384 x 2 at tau 2.5, unstructured inputs, 30 -> 35 us.)
+constexpr int kSplitRows = 64;
+constexpr int kSplitKeys2 = 1792;
+constexpr int kSplitKeys2Listed = 12288;
+inline bool keys_split(int64_t units, int n_keys, bool all_listed) {
+  return units <= 256 || (units <= 2 * 256 && n_keys >= (all_listed ? kSplitKeys2Listed : kSplitKeys2));
+}
+
 // fp16 elements of one (b, h) slab of prepared K (or V).
 inline int64_t prepared_tile_elems(int N) {
   return (int64_t)((N + kPrepTile - 1) / kPrepTile) * kPrepTileElems;

@@ -1594,7 +1594,6 @@ void attn_prepared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 // end, and wave w writes head dims [32w, 32w + 32).  A wave whose probabilities
 // leave the fp16 range marks the whole workgroup's rows for the second pass.
 // Rows and masks as in attn_prepared_kernel; the loop is its dense first pass.
-constexpr int kSplitRows = 64;
 
 template <bool kRope, bool kSparse, bool kRec, bool kOutRec>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
@@ -2058,23 +2057,6 @@ hipError_t launch_prepare_kv_records(const uint8_t* rec, uint16_t* k_prep, uint1
   return hipGetLastError();
 }
 
-// Whether `units` blocks of 64 query rows run with the keys split: when the
-// whole grid takes one round of the 256 CUs that way, or two over at least
-// kSplitKeys2 keys.  A round costs 0.37 of a sweep of whole 256-row tiles, two
-// 0.74, three 1.1, whatever part of a round the last one is (measured: 12,480
-// keys, 195 units 233 -> 86 us; 3,600 keys, 285 units 80 -> 60 us and 570 units
-// 83 -> 90 us; 1,024 keys, 16 units 32 -> 18 us), and each round about 9 us of
-// prologue and epilogue, which a second one pays again: prepare and attention
-// of 192 keys, 255 units 28.9 -> 26.5 us, 384 keys, 240 units 33.4 -> 26.8 us,
-// but 480 units of 384 keys 36.4 -> 46.1 us, of 1,024 48.1 -> 52.6 us, of 1,536
-// 57.0 -> 58.0 us, of 2,048 66.3 -> 63.8 us, of 3,072 84.5 -> 78.3 us.  The
-// rule knows no more than the sizes, so that the block-sparse walk over a full
-// list takes the dense walk's kernel.
-constexpr int kSplitKeys2 = 1792;
-static bool keys_split(int64_t units, int n_keys) {
-  return units <= 256 || (units <= 2 * 256 && n_keys >= kSplitKeys2);
-}
-
 hipError_t launch_attn_fwd_prepared(const uint16_t* q, const uint16_t* k_prep,
                                     const uint16_t* v_prep, void* out_v, int BH,
                                     const SeqGrid& g, int n_kv, const float2* tab,
@@ -2091,7 +2073,7 @@ hipError_t launch_attn_fwd_prepared(const uint16_t* q, const uint16_t* k_prep,
              : n_qtiles;
   const bool orec = out_format == 2;
   const int units = (g.n + kSplitRows - 1) / kSplitRows;  // per slab
-  const bool split = (sparse || nkb == 0) && keys_split((int64_t)units * BH, n_kv);
+  const bool split = (sparse || nkb == 0) && keys_split((int64_t)units * BH, n_kv, sparse && g.nt == 0);
   if (split) {
 #define SOL_SPLIT(R, S, Q) (orec ? attn_keysplit_kernel<R, S, Q, true> : attn_keysplit_kernel<R, S, Q, false>)
     auto* kernel = qrec     ? SOL_SPLIT(false, false, true)

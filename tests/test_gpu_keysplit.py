@@ -1,6 +1,6 @@
 """The key-split first pass (64 query rows a workgroup, a quarter of the keys a
-wave), taken where a grid has at most 256 such units, against whole 256-row
-tiles: the same slabs in a call just over the line.  The two sum the keys in
+wave), taken where a grid has at most 256 such units, or 512 over a long walk,
+against whole 256-row tiles: the same slabs in a call just over the line.  The two sum the keys in
 another order (and round each probability to fp16 alike), so bf16 outputs agree
 to the rounding of the output, and nearly all are equal."""
 import pytest
@@ -123,3 +123,34 @@ def test_overflowing_rows_go_to_the_second_pass():
             outs.append(sol.attn_fwd_prepared_ex(q[:, :s].contiguous(), kp, vp, keys, 0, 0, 0, **how))
         whole = outs[1][:, :, :n] if "int8_records" in how else outs[1][:, :n]
         assert torch.equal(outs[0], whole), how  # both are the second pass's
+
+
+def _sparse(slabs, grid, text, tau, seed):
+    rows = text + grid[0] * grid[1] * grid[2]
+    q, k, v = _qkv(max(slabs), rows, rows, seed)
+    tab = sol.rope3d_table(*grid, device=DEV)
+    outs = []
+    for s in slabs:
+        qs = q[:, :s].contiguous()
+        kp, vp = sol.prepare_kv(k[:, :s].contiguous(), v[:, :s].contiguous(), *grid, tab)
+        ws = sol.sparse_route(qs, kp, *grid, tab, tau)
+        outs.append(sol.attn_fwd_sparse(qs, kp, vp, *grid, tab, ws))
+    return outs
+
+
+# (slabs in two rounds, slabs over them, grid, prefix rows, split)
+LISTED = [(12, 16, (3, 21, 33), 0, False),   # 2,079 tokens, 33 units a slab
+          (12, 16, (3, 21, 32), 63, True),   # as many, a prefix: its query block walks every key
+          (2, 3, (11, 1, 1117), 0, False),   # 12,287 tokens, 192 units a slab
+          (2, 3, (12, 32, 32), 0, True)]     # 12,288
+
+
+@pytest.mark.parametrize("two,over,grid,text,split", LISTED, ids=[str(c) for c in LISTED])
+def test_second_round_of_block_sparse_units(two, over, grid, text, split):
+    """257 to 512 units of a block-sparse call split only where some query block
+    walks every key or the lists are long: elsewhere whole tiles are faster,
+    and the call gives the bits of one past 512 units."""
+    a, b = _sparse((two, over), grid, text, 1.0, 17)
+    b = b[:, :two]
+    assert torch.equal(a, b) != split
+    _check(a, b, "%s + %d" % (grid, text))

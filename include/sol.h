@@ -171,12 +171,12 @@ int sol_qknorm_rope3d(const void* x, void* y, int B, int H, int N, int D, int T,
  * written yet as one: it walks the slabs front to back in chunks, and for a
  * chunk of c slabs prepares their K and V (sol_prepare_kv, 2 c slabs' worth of
  * fp16 tiles) in the out slabs after the chunk, then attends to them
- * (sol_attn_fwd_prepared), writing the chunk's own out slabs; each chunk is as
- * large as the room after it allows, and of these chunks the call keeps the
- * leading ones that a launch-round model says pay (a chunk too small to fill
- * the chip costs more than running its slabs in the fused kernel).  The
- * slabs after the kept chunks (sol_attn_fwd_plan tells how many slabs the
- * chunks cover: 36 of 40 at 720p, none at the low resolution's 24 x 12,480)
+ * (sol_attn_fwd_prepared, always on whole tiles), writing the chunk's own out
+ * slabs; each chunk is as large as the room after it allows, and of these
+ * chunks the call keeps the leading ones that a launch-round model says pay (a
+ * chunk too small to fill the chip costs more than running its slabs in the
+ * fused kernel).  The slabs after the kept chunks (sol_attn_fwd_plan tells how
+ * many slabs the chunks cover: 36 of 40 at 720p, none at the low resolution's 24 x 12,480)
  * run the fused kernel instead, which rotates q and k in its tile
  * loads -- q^ as sol_rope3d, bit for bit; k^, rotated again in every query
  * tile's pass over the keys, in fp32 with the table's hi plane only, within
@@ -235,6 +235,17 @@ int sol_attn_fwd_plan(int B, int H, int N, int D);
  * exactly those row blocks, raising the reference in place as it goes (any
  * score distribution: p480's 1 % of keys x8 runs at the rate of the dense
  * shapes).  out must not overlap q, k_prep or v_prep.
+ *
+ * The first launch of every prepared call (also _ex, _ws, _noalloc, the
+ * block-sparse and the records ones) has two forms: whole tiles of 256 query
+ * rows, or, where so few of them would leave compute units idle, units of 64
+ * rows with the keys split over four waves.  The call's sizes choose: B*H and N
+ * (at most 256 such units in all, or 512 over many keys), n_kv, and whether a
+ * block-sparse call has prefix tokens.  The forms sum a row's keys in another
+ * order, so the same slab may differ in its last bits between calls on either
+ * side of that line -- a head alone, in a batch, or on a rank with a share of
+ * the heads.  Within one form a slab's result is a function of its own data, and
+ * calls of the same sizes repeat it bit for bit.
  *
  * The result differs from the fused kernel's by rounding only (same contract and
  * error bound; the fp16 score operands and the reference max change the last

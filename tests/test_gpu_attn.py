@@ -376,9 +376,12 @@ def test_repeated_runs_are_bitwise_identical(path):
 
 @pytest.mark.parametrize("path", PATHS)
 def test_heads_and_batches_are_independent(path):
-    """A slab's result is a function of its own data (and, for sol_attn_fwd,
-    of which of its two routes it took): every slab of a batched call equals
-    the same slab computed alone by that route, bit for bit."""
+    """A slab's result is a function of its own data and of the kernels that the
+    call takes (for sol_attn_fwd the route of the slab; on the prepared path the
+    form of the first pass, which the call's sizes choose): every slab of a
+    batched call equals the same slab computed alone by that route, bit for
+    bit.  The six slabs here and each alone take the same form
+    (test_gpu_keysplit.py compares the two)."""
     w = W.custom(2, 3, 3, 11, 13, n_text=5, seed_index=702)
     q, k, v = (t.to(DEV) for t in W.make_inputs(w))
     tab = sol.rope3d_table(w.T, w.Hl, w.Wl, device=DEV)

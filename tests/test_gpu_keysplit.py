@@ -154,3 +154,26 @@ def test_second_round_of_block_sparse_units(two, over, grid, text, split):
     b = b[:, :two]
     assert torch.equal(a, b) != split
     _check(a, b, "%s + %d" % (grid, text))
+
+
+def test_a_slab_on_either_side_of_the_line():
+    """A slab's result is a function of its own data and of the form the call's
+    sizes choose: bit for bit the same in every call of one form, whatever its
+    neighbours, and across the line within the rounding of the output."""
+    grid, text = (3, 11, 13), 37  # 466 tokens, 8 units a slab
+    n, over = _slabs(text + grid[0] * grid[1] * grid[2])
+    q, k, v = _qkv(over + 9, text + grid[0] * grid[1] * grid[2], text + grid[0] * grid[1] * grid[2], 23)
+    tab = sol.rope3d_table(*grid, device=DEV)
+
+    def run(at):
+        return sol.attn_fwd_ws(*(x[:, at].contiguous() for x in (q, k, v)), *grid, tab)
+
+    split = {(a, b): run(slice(a, b)) for a, b in ((0, n), (5, 6), (4, 9))}
+    whole = {(a, b): run(slice(a, b)) for a, b in ((0, over), (3, over + 9))}
+    for form, size in ((split, n), (whole, over)):
+        for (first, end), out in form.items():
+            end = min(end, size)
+            assert torch.equal(out[:, :end - first], form[0, size][:, first:end]), (first, end)
+    a, b = split[0, n], whole[0, over][:, :n]
+    assert not torch.equal(a, b)
+    _check(a, b, "across the line")

@@ -125,6 +125,38 @@ def test_overflowing_rows_go_to_the_second_pass():
         assert torch.equal(outs[0], whole), how  # both are the second pass's
 
 
+@pytest.mark.parametrize("keys", [1791, 1792, 2050])
+def test_second_round_of_dense_units(keys):
+    """257 to 512 units split from 1,792 keys on, 256 always, 513 never: a call of
+    whole tiles has the bits of any other, one of split units others."""
+    rows = 513  # 9 units a slab
+    q, k, v = _qkv(57, rows, keys, keys)
+    outs = {}
+    for s in (28, 29, 56, 57):
+        kp, vp = sol.prepared_kv_buffers(1, s, keys, DEV)
+        sol.prepare_kv_ex(k[:, :s].contiguous(), v[:, :s].contiguous(), 0, 0, 0, None, kp, vp)
+        outs[s] = sol.attn_fwd_prepared_ex(q[:, :s].contiguous(), kp, vp, keys, 0, 0, 0)
+    for s in (28, 29, 56):
+        whole = outs[57][:, :s]
+        assert torch.equal(outs[s], whole) == (s != 28 and keys < 1792), s
+        _check(outs[s], whole, "%d slabs, %d keys" % (s, keys))
+
+
+@pytest.mark.parametrize("tokens,split,whole", [(300, 51, 52), (1800, 17, 18)])
+def test_records_equal_whole_tiles(tokens, split, whole):
+    """Queries, keys and values from records: one round of split units (255 of
+    them) and two (493), against whole tiles (260, 522)."""
+    q, k, v = _qkv(whole, tokens, tokens, tokens)
+    outs = []
+    for s in (split, whole):
+        rec = sol.qkv_encode(*(x[:, :s].contiguous() for x in (q, k, v)))
+        kp, vp = sol.prepared_kv_buffers(1, s, tokens, DEV)
+        sol.prepare_kv_records(rec, kp, vp)
+        outs.append(sol.attn_fwd_records(rec, kp, vp))
+    assert not torch.equal(outs[0], outs[1][:, :split])
+    _check(outs[0], outs[1][:, :split], "records, %d tokens" % tokens)
+
+
 def _sparse(slabs, grid, text, tau, seed):
     rows = text + grid[0] * grid[1] * grid[2]
     q, k, v = _qkv(max(slabs), rows, rows, seed)

@@ -103,6 +103,13 @@ def test_mfma_latency_respected(asm_text):
     reload overwrite an accumulator still being read)."""
     kernels = functions(asm_text, "attn_prepared_kernel")
     assert len(kernels) == N_INSTANCES
+    check_mfma_latency(kernels)
+
+
+def check_mfma_latency(kernels, past_branches=True):
+    """past_branches: read on past an unconditional branch, though what follows
+    it in the text does not follow it in time (stricter, and true of a kernel
+    whose blocks end well clear of their MFMAs)."""
     for name, body in kernels:
         ins = instructions(body)
         n_asm = 0
@@ -114,7 +121,7 @@ def test_mfma_latency_respected(asm_text):
             dst, srcc = regs(ops[0]), regs(ops[3])
             ws = 0
             for t2, _ in ins[i + 1:]:
-                if ws >= WAIT_STATES:
+                if ws >= WAIT_STATES or (not past_branches and t2.startswith("s_branch")):
                     break
                 m = re.match(r"s_nop (\d+)", t2)
                 if m:

@@ -9,26 +9,14 @@ import test_kernel_asm as checks
 from test_kernel_asm import asm_text  # noqa: F401  (the fixture)
 
 N_INSTANCES = 10  # (rope, sparse) and records, each with and without output records
-
-
 WRITE_WAIT_STATES = 2  # a VALU write of an MFMA's A, B or C operand
 
 
-def keysplit_only(asm_text):
-    """The key-split kernels as the checks of the prepared kernel find them."""
-    bodies = checks.functions(asm_text, "attn_keysplit_kernel")
-    assert len(bodies) == N_INSTANCES
-    text = "".join("%s:\n%s\n.Lfunc_end\n" % (name.replace("attn_keysplit_kernel", "attn_prepared_kernel"), "\n".join(body))
-                   for name, body in bodies)
-    # what follows an unconditional branch in the text does not follow it in time
-    return re.sub(r"(?m)^(\s*s_branch .*)$", r"\1\n\ts_nop 15", text)
-
-
-def test_latencies_and_spills(asm_text, monkeypatch):  # noqa: F811
-    text = keysplit_only(asm_text)
-    monkeypatch.setattr(checks, "N_INSTANCES", N_INSTANCES)
-    checks.test_mfma_latency_respected(text)
-    checks.test_no_instance_spills(text)
+def test_latencies_and_spills(asm_text):  # noqa: F811
+    kernels = checks.functions(asm_text, "attn_keysplit_kernel")
+    assert len(kernels) == N_INSTANCES
+    checks.check_mfma_latency(kernels, past_branches=False)
+    checks.check_no_spills(kernels)
 
 
 def test_loop_waits(asm_text):  # noqa: F811

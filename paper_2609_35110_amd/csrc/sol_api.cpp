@@ -226,11 +226,15 @@ int sol_rope3d(const void* x, void* y, int B, int H, int N, int D, int T, int Hl
 // leave room for that, up to kMaxChunks chunks.  Of those chunks it keeps the
 // leading ones that make the call fastest by a simple model: a launch over x
 // workgroups takes ceil(x / 256) rounds on the 256 compute units, a round
-// costs 1 on the prepared path and kFusedCost on the fused kernel (measured:
-// 1.4 at 720p and at the low resolution), each chunk adds kChunkCost for its
-// prepare pass and launches, and the slabs after the kept chunks run the
-// fused kernel in one launch.  Returns the number of
-// slabs the kept chunks cover and their sizes in chunk[].
+// costs 1 on the prepared path and kFusedCost on the fused kernel, each chunk
+// adds kChunkCost for its prepare pass and launches, and the slabs after the
+// kept chunks run the fused kernel in one launch.  Returns the number of slabs
+// the kept chunks cover and their sizes in chunk[].
+//
+// kFusedCost is the fused kernel's ratio when the schedule was fixed.  Since its
+// loop runs in slots the same launches measure 1.26 (12,480 tokens x 20 and 24
+// slabs), 1.31 to 1.33 (48,360 x 1 and 2) and 1.28 to 1.37 (111,600 x 1); at 1.3
+// the split of 48,360 x 40 would move, from 36 slabs in place to 31.
 constexpr int kMaxChunks = 64;
 constexpr double kFusedCost = 1.4;
 constexpr double kChunkCost = 0.1;

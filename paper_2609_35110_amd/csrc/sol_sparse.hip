@@ -179,8 +179,9 @@ __global__ __launch_bounds__(256) void pool_k_kernel(const uint4* __restrict__ k
 // r + 64, .. r + 1; the best block is a (score, lowest index) reduction; and
 // the kept blocks are compacted in ascending order with ballots.  kCap: key
 // blocks the score rows hold in LDS.  The usual case (up to 131,072 tokens)
-// takes 21 KB, so that seven workgroups share a CU and hide each other's
-// latency; the rows for the longest sequence would leave room for one.
+// takes 18 KB, so that five workgroups share a CU (their registers' limit; LDS
+// holds eight) and hide each other's latency; the rows for the longest sequence
+// leave room for one.
 // 111,600 tokens of 40 heads: 130 us, against 579 us with one reduction after
 // another over the whole workgroup and rows for the longest sequence.
 constexpr int kRouteQB = 4;

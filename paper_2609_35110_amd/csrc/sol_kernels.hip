@@ -543,7 +543,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     ns1 = f32x16{};
     // a pair's word and row sums: fp32 adds of the unrounded exponentials
     // (v_dot2_f32_f16 of the words is one instruction less a word, but shares
-    // the matrix pipe: 12,480 keys x 24 heads 1.934 against 1.922 ms)
+    // the matrix pipe and gains nothing: 12,480 keys x 24 heads 1.934 against
+    // 1.922 ms in one run, even within the noise in another)
     auto finish = [&](int w) __attribute__((always_inline)) {
       f16x2 h;
       h[0] = (_Float16)pa;
